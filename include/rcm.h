@@ -176,7 +176,13 @@ typedef struct {
                                state fit in one work-group's LDS (about 6,000
                                vertices of a 3D mesh, 7,000 of a 2D mesh) is
                                ordered by one work-group from LDS, in one
-                               launch; others by the persistent team kernel;
+                               launch; of other graphs (at most 2^19 vertices,
+                               label_mode 0, no launch option of the team
+                               kernel set by the caller), and of those in a
+                               batch, each component whose levels are of
+                               moderate width (at most 1,024 or 2,048
+                               vertices) by one work-group with its levels in
+                               LDS; the rest by the persistent team kernel;
                             1 = always the persistent team kernel;
                             2 = always the one-work-group LDS engine
                                (RCM_ERR_INVALID_ARGUMENT if the graph does
@@ -353,7 +359,8 @@ typedef struct {
   int32_t team_pp_levels;    /* levels expanded by the pseudo-peripheral passes */
   int32_t team_label_levels; /* levels of the labelled BFS */
   /* The settings the call used (filled whatever RCM_TIMING says): the
-     engine (1 persistent team kernel, 2 one-work-group LDS engine, 3 the
+     engine (1 a work-group per component or the persistent team kernel, 2
+     one-work-group LDS engine, 3 the
      team kernel, which renumbered the graph after its first level
      structure: see relabel_levels, 4 the same renumbering, after which one
      work-group walked the remaining level structures from an LDS window of
@@ -361,8 +368,10 @@ typedef struct {
      team size, threads per team work-group (with engine 2: 512 for its
      bounded-row variant, whose rows hold at most 8 off-diagonal entries,
      64 for the general one), labelling sub-team and
-     asynchronous round length of the launch with teams (0 if none ran), and
-     the small-component cutoff.  Shows what a tuning table changed.      */
+     asynchronous round length of a launch with teams (0 if none was called
+     for; a single graph in mode 0 shows the settings such a launch would
+     take, whether or not its components came to one), and the
+     small-component cutoff.  Shows what a tuning table changed.      */
   int32_t used_mode;
   int32_t used_team_size;
   int32_t used_block_threads;

@@ -14,6 +14,7 @@
 // the stream a handful of times per call; everything else stays on device.
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <cstdio>
@@ -52,6 +53,9 @@ struct Opts {
   int label_team = 64;
   int search_round = 16;
   int mode = 0;  // 0 auto, 1 team kernel only, 2 one-work-group LDS engine only
+  // components may go to the component engine: the caller neither asked for
+  // the team kernel (mode 1) nor set any of its launch options
+  bool component = true;
   int relabel_levels = 4096;  // renumber a long whole-graph component (0 = never)
   uint32_t shuffle = 0;                 // seed of the work-group / task shuffle
   const int32_t* abort_flag = nullptr;  // the caller's abort flag (host address) ...
@@ -99,6 +103,13 @@ inline bool window_enabled() {
 inline int team_for(const Opts& o, int64_t n) {
   if (o.team_size > 0) return o.team_size;
   return n >= (1 << 18) ? 256 : 64;
+}
+
+// Whether any launch option of the team kernel is set.
+inline bool launch_options_set(const rcm_options& o) {
+  return o.team_size || o.block_threads || o.small_cutoff || o.narrow_cutoff ||
+         o.small_threads || o.max_teams || o.rebalance_levels || o.async_search ||
+         o.label_team || o.search_round;
 }
 
 // Auto values differ for batched calls: many components of many graphs share
@@ -151,6 +162,7 @@ bool parse_options(const rcm_options* o, Opts* out, bool batched = false) {
     r.shuffle = static_cast<uint32_t>(o->shuffle_seed);
     if (o->relabel_levels) r.relabel_levels = o->relabel_levels > 0 ? o->relabel_levels : 0;
     r.abort_flag = o->abort_flag;
+    r.component = o->mode == 0 && o->label_mode == 0 && !launch_options_set(*o);
   }
   *out = r;
   return true;
@@ -185,9 +197,9 @@ Layout make_layout(int64_t n, int64_t nnz, int64_t nseg, bool batched, int teams
   L.visit = take(4 * N);
   L.claim = take(4 * N);
   L.qi = take(16 * N);
+  L.dkey = take(8 * N);
   L.tmp = take(4 * N);
   L.iperm = take(4 * N);
-  L.dkey = take(8 * N);
   L.sizes = take(4 * N);
   L.offs = take(4 * N);
   L.results = take(sizeof(CompResult) * N);
@@ -210,7 +222,7 @@ Layout make_layout(int64_t n, int64_t nnz, int64_t nseg, bool batched, int teams
   if (batched) {
     L.rowptr_g = take(4 * (N + 1));
     L.colidx_g = take(4 * static_cast<size_t>(nnz));
-    L.ell = 0;
+    L.ell = 0;  // see batch_ell
   } else {
     L.rowptr_g = L.colidx_g = 0;
     L.ell = take(4 * kEllWidth * N);
@@ -219,8 +231,28 @@ Layout make_layout(int64_t n, int64_t nnz, int64_t nseg, bool batched, int teams
   return L;
 }
 
+// A batch's row copy, which only the component engine reads, takes the team
+// kernel's visit, claim, qi and dkey regions (32 bytes a vertex), which that
+// kernel's launch sets up afterwards.
+inline int4* batch_ell(const Layout& L, char* ws, size_t n) {
+  static_assert(4 + 4 + 16 + 8 == 4 * kEllWidth, "the four regions hold the copy");
+  return L.tmp - L.visit >= 4 * kEllWidth * n ? reinterpret_cast<int4*>(ws + L.visit) : nullptr;
+}
+
 constexpr int kSmallTeams = 1024;
 constexpr int kWideBatchTeam = 4;  // team size of a batch's many-teams layout
+// Widest level the component engine takes on in vertex 0's component: past
+// it the whole team is the faster (a team's level costs about the same
+// whatever its width).
+constexpr int32_t kHeadWidth = kComponentEllCap;
+// The small device words of a call (misc): [0..2] and [6] the scan's verdict,
+// [4], [5] the component search's, [8..11] task counts, [12..15] the
+// renumbering's and the window engine's, [16] a queue, and:
+constexpr int kCountsAt = 17;  // declined tasks of the component engine, three lists
+constexpr int kProbeAt = 24;   // its probe
+constexpr int kMiscInts = 28;  // what one readback covers
+// Declined components of more vertices than this go to teams.
+constexpr int32_t kDeclinedCutoff = 1 << 14;
 
 // The calling thread's timing events on the current device, created on its
 // first timed call there and kept (creating ten events costs more than a
@@ -362,21 +394,98 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
   int32_t* sched = reinterpret_cast<int32_t*>(ws + L.sched);
 
   if (abort_set(opt)) return RCM_ERR_ABORTED;
-  HIP_TRY(hipMemcpyAsync(seg_off, seg_off_host, sizeof(int32_t) * (g.nseg + 1),
-                         hipMemcpyHostToDevice, s));
+  SetupList setup;
+  if (g.nseg == 1)
+    setup.put(seg_off, int2{0, g.n});
+  else
+    HIP_TRY(hipMemcpyAsync(seg_off, seg_off_host, sizeof(int32_t) * (g.nseg + 1),
+                           hipMemcpyHostToDevice, s));
   g.seg_off = seg_off;
-  HIP_TRY(hipMemsetAsync(misc, 0, 256, s));
-  HIP_TRY(hipMemsetAsync(segstats, 0, sizeof(SegStats) * g.nseg, s));
+  setup.fill(misc, 256, 0);
+  setup.fill(segstats, sizeof(SegStats) * g.nseg, 0);
+  setup.fill(gctl, sizeof(GlobalCtl), 0);
 
   timer.mark(0);
   // 2. checks, degrees, input bandwidth/profile
+  int32_t largest_graph = 0;
+  for (int i = 0; i < g.nseg; ++i)
+    largest_graph = std::max(largest_graph, seg_off_host[i + 1] - seg_off_host[i]);
+  // The component engine takes a graph's components first (one work-group
+  // each, levels of moderate width); it declines the wide ones, and the team
+  // kernel orders those.
+  const bool component = opt.component && largest_graph <= kComponentRange;
   int4* ell = L.ell != 0 && N > 0 ? reinterpret_cast<int4*>(ws + L.ell) : nullptr;
+  if (component && g.nseg > 1) ell = batch_ell(L, ws, N);
+  // the component engine's probe of vertex 0's component (see below)
+  const bool head = g.nseg == 1;
+  const size_t ci_room = L.t_single - L.results - 256;
+  // a long component stops after its first level structure (asynchronous
+  // passes and labelled orders only) when its renumbered columns fit the
+  // component results' region (see below): at most 8 entries per vertex
+  const int32_t renumber_from = head && opt.label_mode == 0 && opt.async_search &&
+                                        4 * static_cast<size_t>(g.nnz) <= ci_room
+                                    ? opt.relabel_levels
+                                    : 0;
+  unsigned long long* dkey = reinterpret_cast<unsigned long long*>(ws + L.dkey);
+  if (head) setup.put(seeds, int32_t{0});
+  if (head && component && renumber_from > 0) setup.fill(dkey, 8 * N, 0);
+  HIP_TRY(launch_setup(&setup, s));
   HIP_TRY(launch_validate_scan(g, vinfo, beta, segstats, misc + 0, misc + 3, ell, misc + 6, s));
-  int32_t h[7];
-  rcm_status st = read_ints(h, misc, 7, s);
+  const bool short_rows = static_cast<int64_t>(g.nnz) <= 8 * static_cast<int64_t>(g.n);
+  ComponentParams C{};
+  C.n = g.n;
+  C.colidx = g.colidx;
+  C.vinfo = vinfo;
+  C.ell = ell_enabled() ? ell : nullptr;
+  C.seg_off = g.seg_off;
+  C.nseg = g.nseg;
+  C.perm = perm_out;
+  C.iperm = iperm;
+  C.results = results;
+  C.probe = reinterpret_cast<ComponentProbe*>(misc + kProbeAt);
+  C.queue = misc + 16;
+  C.counts = misc + kCountsAt;
+  C.declined = tmp;  // the team kernel's child counts, not in use yet
+  C.gctl = gctl;
+  C.short_rows = short_rows ? 1 : 0;
+  C.pp_variant = opt.pp_variant;
+  C.shuffle = opt.shuffle;
+  C.abort_flag = opt.abort_dev;
+  // The component of vertex 0 has the lowest seed of all, so its label block
+  // starts at 0 whatever the other components are: it is ordered first, its
+  // size found by its first level structure, and the search for the other
+  // components only has to cover the vertices it did not reach.  (Single
+  // graphs only; a batch runs the search over every graph.)
+  const int32_t head_anchor = opt.reverse_mode == 1 ? g.n - 1 : -1;
+  if (head && component) {
+    // The component engine's probe of it, right behind the scan, whose
+    // verdict the probe reads on the device: the readback below covers both.
+    ComponentParams probe = C;
+    probe.bad_csr = misc;
+    probe.visit = visit;
+    probe.dkey = renumber_from > 0 ? dkey : nullptr;
+    probe.head = CompTask{0, -1, 0, 0, head_anchor};
+    probe.n_head = 1;
+    probe.width_limit = short_rows ? kHeadWidth : kComponentCap;
+    // (a cube of n vertices has levels of 0.75 n^(2/3) and more; grown from a
+    // corner its level 8 has 3 times the vertices of level 4 or more, a
+    // surface's about twice)
+    probe.growth = std::pow(static_cast<double>(g.n), 2.0 / 3.0) <= probe.width_limit ? 0
+                   : short_rows                                                       ? 28
+                                                                                      : 32;
+    timer.kmark(1, true);
+    HIP_TRY(launch_component(probe, s));
+    timer.kmark(1, false);
+  }
+  int32_t h[kMiscInts];
+  rcm_status st = read_ints(h, misc, kMiscInts, s);
   if (st != RCM_OK) return st;
   if (h[0]) return RCM_ERR_BAD_CSR;
-  // a row longer than the copy's width: the traversal reads the CSR
+  const bool probed = head && component && h[kCountsAt] == 0;
+  ComponentProbe pr{};
+  std::memcpy(&pr, h + kProbeAt, sizeof(pr));
+  // a row longer than the copy's width: the team kernel reads the CSR (the
+  // component engine decides that for each component)
   if (h[6] || !ell_enabled()) ell = nullptr;
   if (h[3]) {
     // rows too long for the scan's own duplicate check
@@ -395,9 +504,6 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
   }
   timer.mark(1);
   // 4-5. components and ordering
-  HIP_TRY(hipMemsetAsync(visit, 0, 4 * N, s));
-  HIP_TRY(hipMemsetAsync(claim, 0xFF, 4 * N, s));
-  HIP_TRY(hipMemsetAsync(gctl, 0, sizeof(GlobalCtl), s));
   BfsParams P;
   P.rowptr = g.rowptr;
   P.colidx = g.colidx;
@@ -420,16 +526,31 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
   P.async_search = opt.async_search;
   P.seg_off = g.seg_off;
   P.nseg = g.nseg;
-  P.dkey = reinterpret_cast<unsigned long long*>(ws + L.dkey);
+  P.dkey = dkey;
   P.abort_flag = opt.abort_dev;
   P.shuffle = opt.shuffle;
   P.relabel_levels = 0;
   P.resume = 0;
   P.relabelled = 0;
   P.new_of_old = nullptr;
-  P.ell = ell;
-  // distance words of the asynchronous passes start below every pass tag
-  if (opt.async_search) HIP_TRY(hipMemsetAsync(P.dkey, 0, 8 * static_cast<size_t>(g.n), s));
+  P.ell = g.nseg == 1 ? ell : nullptr;
+  // Before the first launch of the team kernel: no vertex visited or claimed,
+  // and the distance words of the asynchronous passes below every pass tag.
+  // (After a probe by the component engine that is behind the search for the
+  // other components, which reads the probe's stamps in visit.)
+  bool team_ready = false;
+  auto ready_team = [&]() {
+    if (team_ready) return;
+    team_ready = true;
+    setup.fill(visit, 4 * N, 0);
+    setup.fill(claim, 4 * N, -1);
+    if (opt.async_search) setup.fill(P.dkey, 8 * N, 0);
+  };
+  if (!component) {
+    ready_team();
+    // (a batch's isolated vertices write their keys before the launch)
+    if (!head) HIP_TRY(launch_setup(&setup, s));
+  }
   P.teams = teams;
   P.slots = slots;
   P.sub_slots = reinterpret_cast<TeamSlots*>(ws + L.sub_slots);
@@ -455,11 +576,12 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
   // 2^18 vertices or more (those want large teams), it runs teams of 4 over
   // every resident work-group instead: all large components start at once,
   // and the small ones follow when the team work-groups turn to them.
-  int32_t largest_graph = 0;
-  for (int i = 0; i < g.nseg; ++i)
-    largest_graph = std::max(largest_graph, seg_off_host[i + 1] - seg_off_host[i]);
+  // declined: the tasks are what the component engine left.  They are few and
+  // wide as a rule, so the resident work-groups are shared out among them,
+  // teams of 8 at least (the shares measured on single graphs: a 3D grid of
+  // 195,000 vertices takes 5.0 ms on 8 work-groups, 2.6 ms on 64).
   auto launch = [&](const CompTask* big, int32_t n_big, const CompTask* small, int32_t n_small,
-                    int kslot, bool copy_clk) -> rcm_status {
+                    int kslot, bool copy_clk, bool declined) -> rcm_status {
     P.big_tasks = big;
     P.n_big = n_big;
     P.tasks = small;
@@ -479,6 +601,11 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
         room = resident;
         cap = kMaxConcurrentTeams;
       }
+      if (declined) {
+        team = std::min(8, resident);
+        while (2 * team <= std::min(64, room / n_big)) team *= 2;
+        cap = kMaxConcurrentTeams;
+      }
       P.team_size = team;
       nteams = std::max(1, std::min({n_big, cap, room / team}));
       P.big_blocks = nteams * team;
@@ -490,13 +617,14 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
       blocks = std::min(n_small, kSmallTeams);
     }
     if (blocks <= 0) return RCM_OK;
-    HIP_TRY(hipMemsetAsync(P.queues, 0, 2 * sizeof(int32_t), s));
+    setup.put(P.queues, int2{0, 0});
     if (nteams > 0) {
-      HIP_TRY(hipMemsetAsync(teams, 0, sizeof(TeamCtl) * nteams, s));
-      HIP_TRY(hipMemsetAsync(slots, 0, sizeof(TeamSlots) * nteams, s));
-      HIP_TRY(hipMemsetAsync(P.sub_slots, 0, sizeof(TeamSlots) * nteams, s));
+      setup.fill(teams, sizeof(TeamCtl) * nteams, 0);
+      setup.fill(slots, sizeof(TeamSlots) * nteams, 0);
+      setup.fill(P.sub_slots, sizeof(TeamSlots) * nteams, 0);
     }
-    if (n_small > 0) HIP_TRY(hipMemsetAsync(small_ctl, 0, sizeof(TeamCtl) * blocks, s));
+    if (n_small > 0) setup.fill(small_ctl, sizeof(TeamCtl) * blocks, 0);
+    HIP_TRY(launch_setup(&setup, s));
     if (n_big > 0) {
       g_used[1] = P.team_size;
       g_used[2] = threads;
@@ -515,36 +643,54 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
     }
     return RCM_OK;
   };
-  // The component of vertex 0 has the lowest seed of all, so its label block
-  // starts at 0 whatever the other components are: it is ordered first by
-  // the team, its size found by its first level structure, and the
-  // component search below only has to cover the vertices it did not reach.
-  // (Single graphs only; a batch runs the search over every graph.)
-  const bool head = g.nseg == 1;
+  // what a team launch takes from the options, whether or not one runs
+  auto note_settings = [&]() {
+    g_used[1] = team_auto;
+    g_used[2] = opt.threads;
+    g_used[3] = opt.label_team;
+    g_used[4] = opt.search_round;
+    g_used[5] = opt.small_cutoff;
+  };
   int32_t head_size = 0;
-  if (head) {
-    const CompTask ht{0, -1, 0, 0, opt.reverse_mode == 1 ? g.n - 1 : -1};
-    const CompResult hr{0, 0, 0, 0, 0, 0, 0};
-    HIP_TRY(hipMemcpyAsync(t_big, &ht, sizeof(ht), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(results, &hr, sizeof(hr), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemsetAsync(seeds, 0, sizeof(int32_t), s));
-    // a long component stops after its first level structure (asynchronous
-    // passes and labelled orders only) when its renumbered columns fit the
-    // component results' region (see below): at most 8 entries per vertex
-    const size_t ci_room = L.t_single - L.results - 256;
-    P.relabel_levels = opt.label_mode == 0 && opt.async_search &&
-                               4 * static_cast<size_t>(g.nnz) <= ci_room
-                           ? opt.relabel_levels
-                           : 0;
-    st = launch(t_big, 1, nullptr, 0, 1, true);
-    P.relabel_levels = 0;
-    if (st != RCM_OK) return st;
+  if (head && component) {
+    note_settings();
+    if (opt.abort_flag) {
+      int32_t err = 0;
+      st = read_ints(&err, &gctl->error, 1, s);
+      if (st != RCM_OK) return st;
+      if (err) return RCM_ERR_ABORTED;
+    }
+    if (probed && (pr.size < 1 || pr.size > g.n || pr.ecc < 0 || pr.ecc >= pr.size))
+      return RCM_ERR_HIP;
+    if (probed) head_size = pr.size;
+  }
+  // the probed component is a long one: renumbered below for the window engine
+  const bool probed_long = probed && renumber_from > 0 && window_enabled() &&
+                           pr.ecc + 1 >= renumber_from;
+  bool head_done = !probed;  // ordered completely
+  if (head && (!probed || probed_long)) {
+    const CompTask ht{0, -1, 0, 0, head_anchor};
     int32_t hres[8];
-    HIP_TRY(hipMemcpyAsync(hres, results, sizeof(CompResult), hipMemcpyDeviceToHost, s));
     // error, diag[8], p1_stop, p1_ecc, p1_tag, p1_size, p1_lastkey (two words)
-    int32_t gc[15];
-    st = read_ints(gc, &gctl->error, 15, s);
-    if (st != RCM_OK) return st;
+    int32_t gc[15] = {};
+    if (probed) {
+      gc[9] = 1;
+      gc[10] = pr.ecc;
+      gc[11] = static_cast<int32_t>(kProbeTag);
+      gc[12] = pr.size;
+      std::memcpy(&gc[13], &pr.key, sizeof(pr.key));
+    } else {
+      ready_team();
+      setup.put(t_big, ht);
+      setup.put(results, CompResult{0, 0, 0, 0, 0, 0, 0});
+      P.relabel_levels = renumber_from;
+      st = launch(t_big, 1, nullptr, 0, 1, true, false);
+      P.relabel_levels = 0;
+      if (st != RCM_OK) return st;
+      HIP_TRY(hipMemcpyAsync(hres, results, sizeof(CompResult), hipMemcpyDeviceToHost, s));
+      st = read_ints(gc, &gctl->error, 15, s);
+      if (st != RCM_OK) return st;
+    }
     if (gc[0]) report_device_error(gctl, s);
     if (gc[0] == RCM_ERR_NOT_SYMMETRIC) return RCM_ERR_NOT_SYMMETRIC;
     if (gc[0]) return RCM_ERR_ABORTED;
@@ -581,7 +727,8 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
       // First the window engine: one work-group walks the remaining
       // passes from LDS along the renumbered ids.  It declines a component
       // whose rows or levels do not fit it, and the team kernel then
-      // resumes the ordering on the renumbered copy.
+      // resumes the ordering on the renumbered copy (the component engine,
+      // below, a component that it has probed).
       bool windowed = false;
       if (window_enabled()) {
         unsigned long long lastkey1 = 0;
@@ -618,15 +765,16 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
         windowed = wst == 0;
         // declined: the team kernel's distance words start below every pass
         // tag again
-        if (!windowed) HIP_TRY(hipMemsetAsync(P.dkey, 0, 8 * static_cast<size_t>(g.n), s));
+        if (!windowed && !probed)
+          HIP_TRY(hipMemsetAsync(P.dkey, 0, 8 * static_cast<size_t>(g.n), s));
       }
-      if (!windowed) {
+      if (!windowed && !probed) {
         long long clk_first[32];
         std::memcpy(clk_first, timer.clk, sizeof(clk_first));
         const CompTask rt{0, size1, 0, 0, ht.anchor};
-        HIP_TRY(hipMemcpyAsync(t_big, &rt, sizeof(rt), hipMemcpyHostToDevice, s));
+        setup.put(t_big, rt);
         int32_t* visit2 = csize;  // free again once the renumbering is built
-        HIP_TRY(hipMemsetAsync(visit2, 0, 4 * N, s));
+        setup.fill(visit2, 4 * N, 0);
         const BfsParams saved = P;
         P.colidx = colidx_new;
         P.rowptr = rowptr_new;
@@ -636,7 +784,7 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
         P.relabelled = 1;
         P.resume = 1;
         P.ell = nullptr;  // the copy holds the caller's numbering
-        st = launch(t_big, 1, nullptr, 0, 1, true);
+        st = launch(t_big, 1, nullptr, 0, 1, true, false);
         P = saved;
         if (st != RCM_OK) return st;
         if (timer.on)
@@ -649,13 +797,61 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
       if (gc[0] == RCM_ERR_NOT_SYMMETRIC) return RCM_ERR_NOT_SYMMETRIC;
       if (gc[0]) return RCM_ERR_ABORTED;
       // the other components claim in the caller's numbering from scratch
-      if (size1 < g.n) HIP_TRY(hipMemsetAsync(claim, 0xFF, 4 * N, s));
-      g_used[0] = windowed ? 4 : 3;  // the window engine / the team kernel, renumbered
+      if (size1 < g.n && team_ready) HIP_TRY(hipMemsetAsync(claim, 0xFF, 4 * N, s));
+      // the window engine / the team kernel, renumbered
+      if (windowed || !probed) g_used[0] = windowed ? 4 : 3;
+      head_done = windowed || !probed;
     }
-    head_size = hres[4];
+    if (head_done) head_size = hres[4];
     if (head_size < 1 || head_size > g.n) return RCM_ERR_HIP;
   }
   int32_t ncomp = head ? 1 : 0;
+  // The tasks of the lists, and of vertex 0's component when the component
+  // engine has only probed it: the component engine first, then the team
+  // kernel for those it declined.
+  auto order_tasks = [&](int32_t n_big, int32_t n_small) -> rcm_status {
+    const CompTask* big = t_big;
+    const CompTask* small = t_small;
+    int32_t left[3] = {0, n_big, n_small};
+    if (component) note_settings();
+    if (component && (n_big + n_small > 0 || !head_done)) {
+      if (!head_done) {
+        C.head = CompTask{0, head_size, 0, 0, head_anchor >= 0 ? head_anchor : head_size - 1};
+        C.n_head = 1;
+      }
+      C.big = t_big;
+      C.n_big = n_big;
+      C.small = t_small;
+      C.n_small = n_small;
+      C.width_limit = kComponentCap;
+      if (abort_set(opt)) return RCM_ERR_ABORTED;
+      HIP_TRY(hipMemsetAsync(C.queue, 0, 4 * sizeof(int32_t), s));
+      timer.kmark(0, true);
+      HIP_TRY(launch_component(C, s));
+      timer.kmark(0, false);
+      // how many of each list it declined
+      HIP_TRY(hipMemcpyAsync(left, C.counts, sizeof(left), hipMemcpyDeviceToHost, s));
+      int32_t err = 0;
+      st = read_ints(&err, &gctl->error, 1, s);
+      if (st != RCM_OK) return st;
+      if (err == RCM_ERR_NOT_SYMMETRIC) return RCM_ERR_NOT_SYMMETRIC;
+      if (err) return RCM_ERR_ABORTED;
+      if (left[0] + left[1] + left[2] > 0) {
+        // the declined tasks go to the component search's regions (parent
+        // to csize, free by now: 16 bytes a vertex and 256 at least each,
+        // and a task of 20 bytes stands for two vertices or more, but for
+        // the head)
+        static_assert(sizeof(CompTask) <= 2 * 16, "the declined tasks fit");
+        CompTask* big_left = reinterpret_cast<CompTask*>(ws + L.parent);
+        CompTask* small_left = big_left + left[0] + left[1];
+        HIP_TRY(launch_declined(C, big_left, small_left, s));
+        big = big_left;
+        small = small_left;
+        ready_team();
+      }
+    }
+    return launch(big, left[0] + left[1], small, left[2], 0, false, component);
+  };
   if (head_size < g.n) {
     int32_t* seeds_rest = head ? seeds + 1 : seeds;
     timer.mark(2);
@@ -669,7 +865,9 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
     }
     const int32_t nrest = h[0];
     ncomp += nrest;
-    HIP_TRY(launch_tasks(g, nrest, seeds_rest, csize, opt.small_cutoff, opt.reverse_mode,
+    // (what the component engine declines is wide: worth a team sooner)
+    const int32_t cutoff = component ? kDeclinedCutoff : opt.small_cutoff;
+    HIP_TRY(launch_tasks(g, nrest, seeds_rest, csize, cutoff, opt.reverse_mode,
                          head_size, head ? 1 : 0, t_single, t_small, t_big, misc + 8, sizes, offs,
                          scan_blk, results, sched, s));
     st = read_ints(h, misc + 8, 4, s);
@@ -687,7 +885,10 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
     HIP_TRY(launch_singletons(t_single, n_single, perm_out, iperm,
                               opt.label_mode ? reinterpret_cast<int32_t*>(claim) : nullptr,
                               results, s));
-    st = launch(t_big, n_big, t_small, n_small, 0, false);
+    st = order_tasks(n_big, n_small);
+    if (st != RCM_OK) return st;
+  } else if (!head_done) {
+    st = order_tasks(0, 0);
     if (st != RCM_OK) return st;
   }
   timer.mark(4);
@@ -1075,8 +1276,12 @@ rcm_status order_single(int32_t n, const int32_t* rowptr, const int32_t* colidx,
   HIP_TRY(hipMemcpyAsync(&ends[1], rowptr + n, 4, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   if (tf) {
+    // (the table's launch options are for what the team kernel orders; only
+    // its mode 1 keeps the component engine out)
+    const bool component = o.component;
     rcm_options eff{};
     if (!tuned(ends[1], &eff) || !parse_options(&eff, &o)) return RCM_ERR_INVALID_ARGUMENT;
+    o.component = component && eff.mode != 1;
   }
   if (ends[0] != 0 || ends[1] < 0) return RCM_ERR_BAD_CSR;
   if (ends[1] > 0 && !colidx) return RCM_ERR_INVALID_ARGUMENT;
@@ -1143,7 +1348,9 @@ rcm_status rcm_order_batched(int32_t num_graphs, const int64_t* vtx_offsets,
     if (opts) eff = *opts;
     if (!tuning_apply(tf, N64, NNZ64, num_graphs > 1 ? num_graphs : 2, &eff))
       return RCM_ERR_INVALID_ARGUMENT;
+    const bool component = o.component;  // as for a single graph
     if (!parse_options(&eff, &o, true)) return RCM_ERR_INVALID_ARGUMENT;
+    o.component = component && eff.mode != 1;
   }
   if (stats) std::memset(stats, 0, sizeof(rcm_stats) * num_graphs);
   if (N64 == 0) return RCM_OK;

@@ -282,6 +282,43 @@ struct Graph {
   const int32_t* seg_off; // device int32[nseg+1] vertex offsets of segments
 };
 
+// What a call sets up between its kernels, in one launch: regions filled with
+// a word (their bytes rounded up to 16; regions are 256-byte aligned and
+// padded) and single words.
+struct SetupList {
+  static constexpr int kRegions = 10, kWords = 24;
+  int4* at[kRegions];
+  uint32_t units[kRegions];  // of 16 bytes
+  int32_t value[kRegions];
+  int32_t* word[kWords];
+  int32_t to[kWords];
+  int regions = 0, words = 0;
+  bool full = false;         // more than fits was asked for: launch_setup fails
+  void fill(void* p, size_t bytes, int32_t v) {
+    if (regions == kRegions) {
+      full = true;
+      return;
+    }
+    at[regions] = static_cast<int4*>(p);
+    units[regions] = static_cast<uint32_t>((bytes + 15) / 16);
+    value[regions++] = v;
+  }
+  // the bytes of a struct of words
+  template <class T>
+  void put(void* p, const T& x) {
+    static_assert(sizeof(T) % 4 == 0, "words");
+    if (words + static_cast<int>(sizeof(T) / 4) > kWords) {
+      full = true;
+      return;
+    }
+    for (size_t i = 0; i < sizeof(T) / 4; ++i) {
+      word[words] = static_cast<int32_t*>(p) + i;
+      __builtin_memcpy(&to[words++], reinterpret_cast<const char*>(&x) + 4 * i, 4);
+    }
+  }
+};
+hipError_t launch_setup(SetupList* list, hipStream_t s);  // and empties it
+
 // err: malformed rows (bounds, columns out of range, repeated columns in
 // rows of up to 64 entries); long_rows: set when a row is longer, whose
 // repeated columns launch_dup_long then checks (into err).
@@ -493,6 +530,61 @@ rcm_status order_single(int32_t n, const int32_t* rowptr, const int32_t* colidx,
 // The checks order_single makes before any HIP call: n >= 0, valid options
 // (RCM_ERR_INVALID_ARGUMENT otherwise).
 rcm_status check_call(int32_t n, const rcm_options* opts);
+
+// The component engine (rcm_component.hip): one work-group per component,
+// for components whose levels hold at most kComponentCap vertices, in graphs
+// of at most kComponentRange vertices; it declines the others, which the team
+// kernel then orders.
+constexpr int32_t kComponentCap = 2048;
+constexpr int32_t kComponentEllCap = 1024;  // ... on the fixed-stride rows
+constexpr int32_t kComponentRange = 1 << 19;
+constexpr uint32_t kProbeTag = (1u << 6) | 1u;  // component 0, pass 1
+// The first level structure of vertex 0's component.
+struct ComponentProbe {
+  int32_t ecc;
+  int32_t size;
+  unsigned long long key;      // minimum (degree, id) of its last level
+};
+struct ComponentParams {
+  int32_t n;                   // vertices of the whole (batched) graph
+  const int32_t* colidx;
+  const int4* vinfo;           // row begin, row end, degree, own number
+  const int4* ell;             // null, or BfsParams::ell; a row too long for the
+                               // copy starts with a negative entry
+  const int32_t* seg_off;      // vertex offsets of the graphs, nseg + 1
+  int32_t nseg;
+  int32_t* perm;
+  int32_t* iperm;
+  CompResult* results;
+  ComponentProbe* probe;       // written for a head of unknown size, read to resume it
+  int32_t* visit;              // with a probe: 1 / 0 for the vertices it reached or not
+                               // (not written when it reached all)
+  unsigned long long* dkey;    // null, or with a probe: the distances, for a renumbering
+  CompTask head;               // the tasks: n_head (0 or 1) of vertex 0's component, whose
+  int32_t n_head;              // size is -1 for a probe, and two lists, in this order
+  const CompTask* big;
+  int32_t n_big;
+  const CompTask* small;
+  int32_t n_small;
+  int32_t* queue;              // next task (zeroed before the launch)
+  int32_t* declined;           // per task: 1 = left to the team kernel
+  int32_t* counts;             // declined: head, big, small (zeroed before the launch)
+  GlobalCtl* gctl;             // the launch's error word
+  const int32_t* bad_csr;      // null, or the input scan's verdict: nothing is done
+                               // when it is not 0
+  int32_t short_rows;          // rows hold at most 8 entries on average
+  int32_t width_limit;         // widest level it takes on, at most kComponentCap
+  int32_t growth;              // 0, or: a component of unknown size is declined when its
+                               // level 8 has growth / 10 times the vertices of level 4
+  int32_t pp_variant;
+  uint32_t shuffle;            // 0, or the seed of the task shuffle
+  const int32_t* abort_flag;   // the caller's abort flag, or null
+};
+hipError_t launch_component(const ComponentParams& p, hipStream_t s);
+// The declined tasks, in list order: the head and the large ones, the small
+// ones.
+hipError_t launch_declined(const ComponentParams& p, CompTask* big_out, CompTask* small_out,
+                           hipStream_t s);
 
 // One launch of the ordering kernel over the task lists in p; cooperative
 // (all blocks co-resident) whenever p has multi-work-group teams.
