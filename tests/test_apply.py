@@ -159,3 +159,53 @@ def test_gpu_permute_long_rows():
     lens = np.diff(g.rowptr)
     assert {8192, 8193, 20001} <= set(lens.tolist())
     _check_gpu_permute(g, 4)
+
+
+def _rows_of(lengths, seed):
+    """A matrix (any pattern: the calls below do not need symmetry) whose row
+    i holds lengths[i] distinct columns in random order."""
+    rng = np.random.default_rng(seed)
+    n = len(lengths)
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    cols = [rng.permutation(n)[:k] for k in lengths]
+    colidx = np.concatenate(cols).astype(np.int32) if n else np.zeros(0, np.int32)
+    return I.Graph(n, rowptr, colidx, "rows")
+
+
+# every length at which a row changes hands (a lane's second entry, a wave, a
+# work-group), matrices of one tile of 128 rows, one row less and more, and a
+# few tiles; with and without empty rows
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [1, 7, 127, 128, 129, 1025, 4099])
+@pytest.mark.parametrize("values", [True, False])
+def test_gpu_permute_and_spmv_row_lengths(n, values):
+    import torch
+    from paper_1610_08128_amd import apply
+
+    rng = np.random.default_rng(n)
+    kinds = [[0, 1, 7, 8, 9, 15, 16, 17, 33, 63, 64, 65, 200], [5, 7], [0, 0, 3], [8, 9, 16],
+             [12, 17, 28]]
+    for i, kind in enumerate(kinds):
+        lengths = np.minimum(rng.choice(kind, n), n)
+        g = _rows_of(lengths, 100 * n + i)
+        print(f"case n={n} kind={kind} nnz={g.nnz}", flush=True)
+        perm = rng.permutation(n).astype(np.int32)
+        iperm = np.empty_like(perm)
+        iperm[perm] = np.arange(n, dtype=np.int32)
+        vals = rng.standard_normal(g.nnz) if values else None
+        want = oracle.permute_csr(g.n, g.rowptr, g.colidx, perm, vals)
+        dev = [torch.from_numpy(t).cuda() if t is not None else None
+               for t in (g.rowptr, g.colidx, perm, iperm, vals)]
+        got = apply.permute(*dev)
+        assert np.array_equal(got[0].cpu().numpy(), want[0])
+        assert np.array_equal(got[1].cpu().numpy(), want[1])
+        if values:
+            assert np.array_equal(got[2].cpu().numpy(), want[2])
+        # two summation orders of a row of L terms: each within L u of the
+        # exact sum, u = 2^-53
+        x = rng.standard_normal(n)
+        y = apply.spmv(dev[0], dev[1], torch.from_numpy(x).cuda(), dev[4]).cpu().numpy()
+        exact = oracle.spmv(g.n, g.rowptr, g.colidx, x, vals)
+        total = oracle.spmv(g.n, g.rowptr, g.colidx, np.abs(x),
+                            np.abs(vals) if values else None)
+        assert np.all(np.abs(y - exact) <= 2 * lengths * 2.0**-53 * total)
