@@ -910,7 +910,7 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
                                ws + L.qi, ws + L.t_single, temp_have, s));
   }
   // 6. result statistics
-  HIP_TRY(launch_bw_after(g, perm_out, iperm, beta, segstats, s));
+  HIP_TRY(launch_bw_after(g, head ? ell : nullptr, perm_out, iperm, beta, segstats, s));
   HIP_TRY(launch_comp_stats(g, ncomp, seeds, results, comp_seg_off, segstats,
                             opt.label_mode == 0 || opt.pp_variant == 1 ? 1 : 0, s));
   if (stats_host) {

@@ -346,8 +346,9 @@ hipError_t launch_tasks(const Graph& g, int32_t ncomp, const int32_t* seeds, con
 // key (nullable): the level orders' key of an isolated vertex, its position
 hipError_t launch_singletons(const CompTask* tasks, int32_t count, int32_t* perm, int32_t* iperm,
                              int32_t* key, CompResult* results, hipStream_t s);
-hipError_t launch_bw_after(const Graph& g, const int32_t* perm, const int32_t* iperm,
-                           int32_t* beta, SegStats* seg, hipStream_t s);
+// ell: the fixed-stride copy of every row, or null
+hipError_t launch_bw_after(const Graph& g, const int4* ell, const int32_t* perm,
+                           const int32_t* iperm, int32_t* beta, SegStats* seg, hipStream_t s);
 hipError_t launch_comp_stats(const Graph& g, int32_t ncomp, const int32_t* seeds,
                              const CompResult* results, int32_t* comp_seg_off, SegStats* seg,
                              int32_t labelled_bfs, hipStream_t s);

@@ -223,3 +223,21 @@ def test_shuffled_tasks_and_abort_in_flight():
         flag.clear()
         again = _order(g, abort_flag=flag, relabel_levels=-1)
     assert all(np.array_equal(x, y) for x, y in zip(want[:2], again[:2])) and want[2] == again[2]
+
+
+@pytest.mark.parametrize("n", [1, 2, 127, 128, 129, 1023, 1025, 16384, 16385])
+@pytest.mark.parametrize("copy", ["1", "0"])
+def test_statistics_of_the_result(n, copy, monkeypatch):
+    """Bandwidth and profile of the result, read from the row copy or the
+    CSR, at the edges of their tiles of 128 rows and 16,384 sums, with rows of
+    the diagonal alone, of one and of many entries."""
+    monkeypatch.setenv("RCM_ELL", copy)
+    rng = np.random.default_rng(n)
+    u = rng.integers(0, n, n // 2)
+    v = rng.integers(0, n, n // 2)
+    keep = u != v
+    g = I.from_edges(n, u[keep], v[keep], name=f"sparse_{n}")
+    _check(g, mode=1)
+    if n > 2:
+        _check(I.from_edges(n, np.zeros(n - 1, np.int64), np.arange(1, n), diag=False,
+                            perm=rng.permutation(n), name=f"star_{n}"), mode=1)
