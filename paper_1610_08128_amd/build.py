@@ -19,8 +19,8 @@ OUT = os.path.join(PKG, "librcm.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
 
 SOURCES = ["rcm_prep.hip", "rcm_bfs.hip", "rcm_api.hip", "rcm_server.hip", "rcm_apply.hip",
-           "rcm_levelorder.hip", "rcm_noalloc.hip", "rcm_small.hip", "rcm_small_ell.hip", "rcm_tuning.hip",
-           "rcm_relabel.hip", "rcm_window.hip", "rcm_component.hip"]
+           "rcm_levelorder.hip", "rcm_noalloc.hip", "rcm_small.hip", "rcm_small_ell.hip",
+           "rcm_small_wide.hip", "rcm_tuning.hip", "rcm_relabel.hip", "rcm_window.hip", "rcm_component.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

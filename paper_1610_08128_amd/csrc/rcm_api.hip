@@ -1171,9 +1171,11 @@ bool order_small(int32_t n, const int32_t* rowptr, const int32_t* colidx, int32_
     return true;
   }
   SmallResult h{};
-  auto run_kernel = [&](bool ell) -> bool {
-    const hipError_t e =
-        ell ? launch_small_ell(job, so, s) : launch_small_order(job, nullptr, 1, so, s);
+  enum Variant { kBoundedRows, kLongRows, kGeneral };
+  auto run_kernel = [&](Variant v) -> bool {
+    const hipError_t e = v == kBoundedRows ? launch_small_ell(job, so, s)
+                         : v == kLongRows  ? launch_small_wide(job, so, s)
+                                           : launch_small_order(job, nullptr, 1, so, s);
     if (e != hipSuccess) return false;
     if (host == nullptr && hipMemcpyAsync(&h, res, sizeof(h), hipMemcpyDeviceToHost, s) !=
                                hipSuccess)
@@ -1189,12 +1191,22 @@ bool order_small(int32_t n, const int32_t* rowptr, const int32_t* colidx, int32_
   const bool try_ell = small_ell_enabled() && small_ell_lds_bytes(n) <= limit;
   bool ok = true;
   if (try_ell) {
-    ok = run_kernel(true);
+    ok = run_kernel(kBoundedRows);
     g_used[2] = 512;
   }
   if (ok && (!try_ell || h.status == kSmallDeclined)) {
-    ok = run_kernel(false);
-    g_used[2] = 64;
+    // A graph with a long row: 16 waves, several lanes a row, wherever they
+    // fit (mean rows of 12, 500 / 2,000 / 4,000 vertices: 391 -> 103, 1,228 ->
+    // 191, 2,201 -> 301 us; of 5, 3,000 vertices: 832 -> 234; a band of 4,000
+    // whose levels are 4 wide: 10.0 -> 3.6 ms).  Only the smallest graphs of
+    // short rows keep the one wave, and the block threads they have always
+    // reported (166 vertices, mean row 5: 216 against 104 us).  Where the
+    // bounded-row engine was not asked, the entry count is not known here.
+    const bool wide = try_ell && (n >= 256 || h.nnz > 8 * static_cast<int64_t>(n)) &&
+                      small_wide_lds_bytes(n, h.nnz) <= limit;
+    if (wide) job.nnz = h.nnz;
+    ok = run_kernel(wide ? kLongRows : kGeneral);
+    g_used[2] = wide ? 1024 : 64;
   }
   if (!ok) *out = RCM_ERR_HIP;
   timer.kmark(0, false);

@@ -515,6 +515,12 @@ hipError_t launch_window_order(const WinParams& P, hipStream_t s);
 size_t small_ell_lds_bytes(int64_t n);
 hipError_t launch_small_ell(const SmallJob& job, const SmallOpts& opts, hipStream_t s);
 
+// The 16-wave variant for long rows (rcm_small_wide.hip) for one graph whose
+// entry count the host knows (job.nnz): LDS bytes it needs (SIZE_MAX outside
+// its sizes) and its launch.
+size_t small_wide_lds_bytes(int64_t n, int64_t nnz);
+hipError_t launch_small_wide(const SmallJob& job, const SmallOpts& opts, hipStream_t s);
+
 // Tuning tables (rcm_tuning.hip): the file named by opts->tuning_file, else
 // by RCM_TUNING_FILE, else none (nullptr).  tuning_apply sets every launch
 // option of *opts still at 0 from the table's entry for the call's size
