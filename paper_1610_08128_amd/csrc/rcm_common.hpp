@@ -494,7 +494,7 @@ struct WinParams {
   const int4* vinfo;              // (row begin, row end, degree, caller id)
   const int32_t* new_of_old;      // caller id -> renumbered id
   uint2* ell;                     // [size] row records the launch builds (workspace)
-  int32_t* ell_flag;              // set when a row does not fit its record
+  int32_t* ell_flag;              // the records' reach, or that a row does not fit one
   uint32_t* claim;                // [size] claim words (workspace), the window's store
   int32_t* order;                 // [size] the labelled order (workspace)
   int32_t ecc1;                   // the first level structure: eccentricity ...

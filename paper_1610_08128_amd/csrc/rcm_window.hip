@@ -40,6 +40,7 @@ namespace {
 constexpr int kWThreads = 512;
 constexpr int32_t kWS = 8192;              // window: vertex ids held in LDS (a power of two)
 constexpr int32_t kWQ = 2048;              // queue entries per level
+constexpr int32_t kWTooFar = 1 << 16;       // *ell_flag: some row does not fit its record
 constexpr int32_t kWMargin = 64;           // ids kept beyond a slide's target range
 // Claim words: kWFree unclaimed; label + 1 in a labelled pass (below 2^29);
 // a search's token (7 - pass) << 29 | (level + 1) << 9 | lane << 3 | slot,
@@ -56,7 +57,7 @@ enum : int32_t { kRun = 0, kSlide = 1, kPassDone = 2, kDecline = 3, kAsym = 4, k
 struct WLds {
   uint2* row;                   // [kWS] four 16-bit offsets to the sorted neighbours (0: filler)
   uint32_t* claim;              // [kWS] claim words of the window's ids
-  int32_t* q[2];                // [kWQ] each: the current and the next level
+  int32_t* q;                   // [2][kWQ]: the current and the next level
 };
 
 struct WCtl {
@@ -138,17 +139,30 @@ __device__ __forceinline__ void row_part(const WLds& L, int32_t x, uint32_t sub,
 // below them).
 __device__ void slide(const WLds& L, WCtl& C, const WinParams& P, int32_t new_lo, bool fresh) {
   const int32_t old_lo = C.w_lo;
-  for (int32_t s = threadIdx.x; s < kWS; s += kWThreads) {
-    const int32_t old_id = old_lo + static_cast<int32_t>(wslot(s - old_lo));
-    const int32_t new_id = new_lo + static_cast<int32_t>(wslot(s - new_lo));
-    if (!fresh && old_id == new_id) continue;
-    if (!fresh && old_id >= 0 && old_id < P.size) P.claim[old_id] = L.claim[s];
-    if (new_id >= 0 && new_id < P.size) {
-      L.row[s] = P.ell[new_id];
-      L.claim[s] = P.claim[new_id];
-    } else {
-      L.row[s] = make_uint2(0, 0);
-      L.claim[s] = kWFree;
+  // kBatch slots a thread at a time, whose loads are all on their way before
+  // the first is waited for (slots that stay load what they hold, unused)
+  constexpr int kBatch = 8;
+  static_assert(kWS % (kWThreads * kBatch) == 0, "even shares");
+  for (int32_t s0 = threadIdx.x; s0 < kWS; s0 += kWThreads * kBatch) {
+    uint2 row[kBatch];
+    uint32_t claim[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int32_t id = new_lo + static_cast<int32_t>(wslot(s0 + j * kWThreads - new_lo));
+      const int32_t at = id < 0 ? 0 : (id < P.size ? id : P.size - 1);
+      row[j] = P.ell[at];
+      claim[j] = P.claim[at];
+    }
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      const int32_t s = s0 + j * kWThreads;
+      const int32_t old_id = old_lo + static_cast<int32_t>(wslot(s - old_lo));
+      const int32_t new_id = new_lo + static_cast<int32_t>(wslot(s - new_lo));
+      if (!fresh && old_id == new_id) continue;
+      if (!fresh && old_id >= 0 && old_id < P.size) P.claim[old_id] = L.claim[s];
+      const bool real = new_id >= 0 && new_id < P.size;
+      L.row[s] = real ? row[j] : make_uint2(0, 0);
+      L.claim[s] = real ? claim[j] : kWFree;
     }
   }
   __syncthreads();
@@ -182,8 +196,8 @@ __device__ int32_t wlevel(const WLds& L, const WinParams& P, int32_t w_lo, int32
   constexpr int32_t kPer = 64 / LPV;
   const uint32_t lane = threadIdx.x;
   const uint32_t sub = lane % LPV;
-  const int32_t* qc = L.q[cur];
-  int32_t* qn = L.q[cur ^ 1];
+  const int32_t* qc = L.q + cur * kWQ;
+  int32_t* qn = L.q + (cur ^ 1) * kWQ;
   const bool one = F <= kPer;
   // every id the level touches must be in the window; a one-chunk level
   // checks the row it has just read, a wider one reads every chunk first
@@ -332,6 +346,79 @@ __device__ int32_t wlevel(const WLds& L, const WinParams& P, int32_t w_lo, int32
   return placed;
 }
 
+// Minimum and maximum over a wave: within the DPP rows, then the four of them.
+__device__ __forceinline__ int32_t uniform(int32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+template <int kCtrl>
+__device__ __forceinline__ int32_t dpp_of(int32_t x) {
+  return __builtin_amdgcn_update_dpp(x, x, kCtrl, 0xf, 0xf, false);
+}
+template <typename Op>
+__device__ __forceinline__ int32_t wave_fold(int32_t x, Op op) {
+  x = op(x, dpp_of<0xB1>(x));   // quad_perm: lane ^ 1
+  x = op(x, dpp_of<0x4E>(x));   // quad_perm: lane ^ 2
+  x = op(x, dpp_of<0x141>(x));  // row_half_mirror
+  x = op(x, dpp_of<0x140>(x));  // row_mirror
+  const int32_t a = __builtin_amdgcn_readlane(x, 0), b = __builtin_amdgcn_readlane(x, 16);
+  const int32_t c = __builtin_amdgcn_readlane(x, 32), d = __builtin_amdgcn_readlane(x, 48);
+  return op(op(a, b), op(c, d));
+}
+
+// One level of at most 64 / LPV vertices whose neighbours are known to be in
+// the window, by the first wave: what wlevel does, without its checks.  Lanes
+// past the level stand for its last vertex, with a label that wins nothing.
+// A search marks with the least word of its pass, and the lane that finds a
+// word above the pass's finds the vertex.  Returns the vertices placed, or a
+// number that makes the labels exceed the component (nothing written then).
+template <int S, int LPV, bool kLabel>
+__device__ __forceinline__ int32_t near_level(const WLds& L, int32_t* __restrict__ order,
+                                              int32_t cur, int32_t F, uint32_t mark, int32_t b,
+                                              int32_t e, int32_t size) {
+  const int32_t lane = threadIdx.x;
+  const int32_t i = lane / LPV;
+  const int32_t x = L.q[cur * kWQ + (i < F ? i : F - 1)];
+  int32_t* qn = L.q + (cur ^ 1) * kWQ;
+  int32_t nb[S];
+  row_part<S>(L, x, static_cast<uint32_t>(lane % LPV), nb);
+  bool win[S];
+  if (kLabel) {
+    const uint32_t mine = static_cast<uint32_t>(b + i) + 1u;
+#pragma unroll
+    for (int j = 0; j < S; ++j) atomicMin(&L.claim[wslot(nb[j])], mine);
+    wfence();
+#pragma unroll
+    for (int j = 0; j < S; ++j) win[j] = lds_ld32(&L.claim[wslot(nb[j])]) == mine;
+    // (a lane past the level never holds the least label, and a row's
+    // fillers name its own vertex, which an earlier label holds)
+  } else {
+    const uint32_t top = mark | ((1u << kWPassShift) - 1u);
+    uint32_t old[S];
+#pragma unroll
+    for (int j = 0; j < S; ++j) old[j] = atomicMin(&L.claim[wslot(nb[j])], mark);
+#pragma unroll
+    for (int j = 0; j < S; ++j) win[j] = old[j] > top;
+  }
+  int total = 0, at = 0;
+#pragma unroll
+  for (int j = 0; j < S; ++j) {
+    const unsigned long long m = __ballot(win[j]);
+    total += __popcll(m);
+    at = static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+        static_cast<uint32_t>(m >> 32),
+        __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), static_cast<uint32_t>(at))));
+  }
+  if (kLabel && e + total > size) return total;
+#pragma unroll
+  for (int j = 0; j < S; ++j) {
+    if (win[j]) {
+      qn[at] = nb[j];
+      if (kLabel) order[e + at] = nb[j];
+    }
+    at += win[j] ? 1 : 0;
+  }
+  wfence();
+  return total;
+}
+
 struct PassOut {
   int32_t ecc;
   int32_t count;
@@ -345,27 +432,96 @@ struct PassOut {
 template <bool kLabel>
 __device__ PassOut window_pass(const WLds& L, WCtl& C, const WinParams& P, int32_t root,
                                uint32_t pass, uint32_t& polls) {
-  const bool w0 = threadIdx.x < 64;
+  // (scalar, and so is what the first wave keeps)
+  const bool w0 = uniform(static_cast<int32_t>(threadIdx.x) >> 6) == 0;
   int32_t start_lo = root - kWS / 2;
   slide(L, C, P, start_lo, true);
   // first-wave state, kept across the slides
-  int32_t cur = 0, F = 1, level = 0, b = 0, e = 1, count = 1;
+  int32_t cur = 0, F = 1, level = 0, b = 0, e = 1;
   const uint32_t passw = (kWPassTop - pass) << kWPassShift;
   if (threadIdx.x == 0) {
-    L.q[0][0] = root;
-    L.claim[wslot(root)] = kLabel ? 1u : passw;
+    L.q[0] = root;
+    L.claim[wslot(root)] = kLabel ? 0u : passw;
     if (kLabel) P.order[0] = root;
   }
   __syncthreads();
   PassOut out{0, 0, kMaxKey, kPassDone};
+  // the last level is q[cur][0, F): its minimum (degree, caller id)
+  auto last_level = [&]() -> int32_t {
+    unsigned long long k = kMaxKey;
+    for (int32_t i = threadIdx.x; i < F; i += 64) {
+      const int4 vi = P.vinfo[L.q[cur * kWQ + i]];
+      const unsigned long long kv = pack_key(vi.z, vi.w);
+      k = kv < k ? kv : k;
+    }
+    k = wave_min_u64(k);
+    if (threadIdx.x == 0) {
+      C.ecc = level;
+      C.count = e;
+      C.lastkey = k;
+    }
+    return kPassDone;
+  };
   while (true) {
     if (w0) {
       int32_t st = kRun;
       int32_t need_lo = 0, need_hi = 0;
-      const int32_t w_lo = C.w_lo;
+      const int32_t w_lo = __builtin_amdgcn_readfirstlane(C.w_lo);
+      // Levels are walked without checks as long as the window holds what
+      // they can touch: an id differs from its neighbours' by at most reach.
+      const int32_t reach = __builtin_amdgcn_readfirstlane(*P.ell_flag) + 1;
       while (st == kRun) {
+        if (F <= 64) {
+          const int32_t lane = threadIdx.x;
+          const int32_t x = L.q[cur * kWQ + (lane < F ? lane : 0)];
+          const int32_t lo = wave_fold(x, [](int32_t p, int32_t q) { return p < q ? p : q; });
+          const int32_t hi = wave_fold(x, [](int32_t p, int32_t q) { return p > q ? p : q; });
+          const int32_t below = lo - w_lo, above = w_lo + kWS - 1 - hi;
+          int32_t safe = (below < above ? below : above) / reach;
+          safe = safe < kWMaxLevel - level ? safe : kWMaxLevel - level;
+          if (safe > 0) {
+            polls += static_cast<uint32_t>(safe);
+            int32_t placed, f = uniform(F), c = uniform(cur), lb = uniform(b), le = uniform(e);
+            int32_t todo = uniform(safe);
+            do {
+              if (f <= 16)
+                placed = near_level<1, 4, kLabel>(L, P.order, c, f, passw, lb, le, P.size);
+              else if (f <= 32)
+                placed = near_level<2, 2, kLabel>(L, P.order, c, f, passw, lb, le, P.size);
+              else
+                placed = near_level<4, 1, kLabel>(L, P.order, c, f, passw, lb, le, P.size);
+              placed = uniform(placed);
+              if (placed == 0) break;
+              lb = le;
+              le += placed;
+              f = placed;
+              c ^= 1;
+              --todo;
+            } while (todo > 0 && f <= 64 && le <= P.size);
+            level += safe - todo;
+            F = f;
+            cur = c;
+            b = lb;
+            e = le;
+            if (e > P.size) {
+              st = kAsym;
+              break;
+            }
+            if (placed != 0) {
+              if (P.abort_flag != nullptr && (polls >> 12) != 0) {
+                polls = 0;
+                const int hit = threadIdx.x == 0 && abort_requested(P.abort_flag) ? 1 : 0;
+                if (__shfl(hit, 0, 64)) st = kAbort;
+              }
+              continue;
+            }
+            st = last_level();
+            break;
+          }
+        }
         // every 4096 levels: the caller's abort flag
-        if (P.abort_flag != nullptr && ((++polls) & 4095u) == 0) {
+        if (P.abort_flag != nullptr && (++polls >> 12) != 0) {
+          polls = 0;
           const int hit = threadIdx.x == 0 && abort_requested(P.abort_flag) ? 1 : 0;
           if (__shfl(hit, 0, 64)) {
             st = kAbort;
@@ -384,6 +540,7 @@ __device__ PassOut window_pass(const WLds& L, WCtl& C, const WinParams& P, int32
           placed = wlevel<2, 2, kLabel>(L, P, w_lo, cur, F, tok, b, e, &need_lo, &need_hi);
         else
           placed = wlevel<4, 1, kLabel>(L, P, w_lo, cur, F, tok, b, e, &need_lo, &need_hi);
+        placed = uniform(placed);
         if (placed == -1) {
           int32_t nl = 0;
           st = slide_target(need_lo, need_hi, w_lo, &nl) ? kSlide : kDecline;
@@ -395,29 +552,15 @@ __device__ PassOut window_pass(const WLds& L, WCtl& C, const WinParams& P, int32
           break;
         }
         if (placed == 0) {
-          // the last level is q[cur][0, F): its minimum (degree, caller id)
-          unsigned long long k = kMaxKey;
-          for (int32_t i = threadIdx.x; i < F; i += 64) {
-            const int4 vi = P.vinfo[L.q[cur][i]];
-            const unsigned long long kv = pack_key(vi.z, vi.w);
-            k = kv < k ? kv : k;
-          }
-          k = wave_min_u64(k);
-          if (threadIdx.x == 0) {
-            C.ecc = level;
-            C.count = count;
-            C.lastkey = k;
-          }
-          st = kPassDone;
-          break;
-        }
-        count += placed;
-        if (count > P.size) {
-          st = kAsym;
+          st = last_level();
           break;
         }
         b = e;
         e += placed;
+        if (e > P.size) {
+          st = kAsym;
+          break;
+        }
         F = placed;
         cur ^= 1;
         ++level;
@@ -452,15 +595,13 @@ __global__ void __launch_bounds__(kWThreads) k_window_order(WinParams P) {
     p += 8 * kWS;
     L.claim = reinterpret_cast<uint32_t*>(p);
     p += 4 * kWS;
-    L.q[0] = reinterpret_cast<int32_t*>(p);
-    p += 4 * kWQ;
-    L.q[1] = reinterpret_cast<int32_t*>(p);
+    L.q = reinterpret_cast<int32_t*>(p);
   }
   if (threadIdx.x == 0) {
     C.w_lo = 0;
     C.state = kRun;
   }
-  if (*P.ell_flag != 0) {
+  if (*P.ell_flag >= kWTooFar) {
     // a row longer than the records hold: the team kernel takes the component
     if (threadIdx.x == 0) *P.status = kWindowDeclined;
     return;
@@ -561,11 +702,13 @@ __global__ void __launch_bounds__(kWThreads) k_window_order(WinParams P) {
 
 // Rows of the renumbered component as records of 4 columns sorted by
 // (degree, caller id), each the 16-bit offset of the neighbour's id from the
-// vertex's (0 for a filler); *flag = 1 when a row has more than 4
-// off-diagonal entries or a neighbour further than an offset reaches.
+// vertex's (0 for a filler); *flag = the largest distance of an id from its
+// neighbours', or kWTooFar when a row has more than 4 off-diagonal entries or
+// a neighbour further than an offset reaches.
 __global__ void k_build_ell4(int32_t size, const int32_t* __restrict__ colidx,
                              const int4* __restrict__ vinfo, uint2* __restrict__ ell,
                              int32_t* __restrict__ flag) {
+  int32_t far = 0;
   for (int32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < size;
        x += gridDim.x * blockDim.x) {
     const int4 r = vinfo[x];
@@ -586,13 +729,15 @@ __global__ void k_build_ell4(int32_t size, const int32_t* __restrict__ colidx,
           break;
         }
         const int4 vy = vinfo[y];
+        const int32_t d = y > x ? y - x : x - y;
+        far = d > far ? d : far;
         ids[c] = y;
         k[c] = pack_key(vy.z, vy.w);
         ++c;
       }
     }
     if (longrow) {
-      atomicOr(flag, 1);
+      far = kWTooFar;
       continue;
     }
     // 5-comparator sorting network for four keys
@@ -615,6 +760,9 @@ __global__ void k_build_ell4(int32_t size, const int32_t* __restrict__ colidx,
                            static_cast<uint32_t>(ids[3] - x) & 0xFFFFu};
     ell[x] = make_uint2(o[0] | o[1] << 16, o[2] | o[3] << 16);
   }
+  // (one atomic a wave, and only where it raises the value)
+  far = wave_max_i32(far);
+  if ((threadIdx.x & 63) == 0 && far > ld_relaxed(flag)) atomicMax(flag, far);
 }
 
 constexpr size_t kWindowLds = 8 * kWS + 4 * kWS + 2 * 4 * kWQ;
