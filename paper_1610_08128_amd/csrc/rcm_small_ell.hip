@@ -13,14 +13,19 @@
 //   children in Algorithm 3 are then already in SortPerm's order along its
 //   row: a child's rank among its siblings is the number of children before
 //   it in the row, a popcount.
-// - Every pass claims vertices with LDS atomic minimums that return
-//   nothing, and reads the words back once: in a search the claim is a
-//   (level, lane, slot) token and the lane that finds its own token back
-//   found the vertex; in the labelled BFS it is the parent's label + 1, and
-//   the minimum is Algorithm 3's smallest parent label.  A level is then
-//   three dependent LDS round trips (its queue entries, their rows, the
-//   claims read back) and no exchange-with-return atomics, which cost a
-//   full round trip each.
+// - Every pass claims vertices with LDS atomic minimums.  In the labelled
+//   BFS the claim is the parent's label + 1, the minimum is Algorithm 3's
+//   smallest parent label, and the words are read back once.  In a search
+//   the lane whose minimum finds a word above the pass's found the vertex
+//   (on levels wider than the wave the claim is a (level, lane, slot) token
+//   instead, found back by its own lane).  A level is then three dependent
+//   LDS round trips: its queue entries, their rows, the claims.
+// - A level of at most 64 vertices, which is what such graphs mostly have,
+//   takes one pass of the wave without a test per column (ell_near_level),
+//   and what the level loops keep is scalar: both are a third of the
+//   instructions, which is what a level's time was (the 64 x 64 grid: 0.45
+//   us a search level and 0.40 a labelled one before, 0.30 and 0.29 now;
+//   the call 218 -> 164 us, the 32 x 32 grid's 92 -> 76).
 // - The bulk phases (loading with the checks, the row sort, the statistics
 //   of the result) run on eight waves; the level loops, whose levels are a
 //   wave wide on such graphs, run on the first wave alone while the others
@@ -177,6 +182,60 @@ __device__ __forceinline__ uint32_t ell_level_key(const ELds& L, int32_t b, int3
   return wave_min_u32(k);
 }
 
+// A value that is the same in every lane, as a scalar.
+__device__ __forceinline__ int32_t uniform(int32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+
+// One level of at most 64 / LPV vertices ord[b, e), either kind of pass: lanes
+// past the level stand for its last vertex.  A search marks with the least
+// word of its pass, and the lane that finds a word above the pass's finds the
+// vertex; in the labelled BFS the lanes read their claims back, and a lane
+// past the level never holds the least label.  A row's fillers name its own
+// vertex, whose word is below either.  Returns the vertices placed.
+template <int S, int LPV, bool kLabel, bool kCheck>
+__device__ __forceinline__ int32_t ell_near_level(const ELds& L, int32_t b, int32_t e,
+                                                  uint32_t passw, uint32_t& lowest) {
+  const int32_t i = b + static_cast<int32_t>(threadIdx.x) / LPV;
+  const uint32_t u = L.ord[i < e ? i : e - 1];
+  uint32_t nb[S];
+  load_part<S>(L, u, threadIdx.x % LPV, nb);
+  bool win[S];
+  if (kLabel) {
+    const uint32_t mine = static_cast<uint32_t>(i) + 1u;
+#pragma unroll
+    for (int j = 0; j < S; ++j) atomicMin(&L.clm[nb[j]], mine);
+    lds_fence();
+#pragma unroll
+    for (int j = 0; j < S; ++j) win[j] = lds_ld(&L.clm[nb[j]]) == mine;
+  } else {
+    const uint32_t top = passw | ((1u << kPassShift) - 1u);
+    uint32_t old[S];
+#pragma unroll
+    for (int j = 0; j < S; ++j) old[j] = atomicMin(&L.clm[nb[j]], passw);
+#pragma unroll
+    for (int j = 0; j < S; ++j) {
+      win[j] = old[j] > top;
+      if (kCheck) lowest = old[j] < lowest ? old[j] : lowest;
+    }
+  }
+  int32_t total = 0;
+  uint32_t at = static_cast<uint32_t>(e);
+#pragma unroll
+  for (int j = 0; j < S; ++j) {
+    const unsigned long long m = __ballot(win[j]);
+    total += __popcll(m);
+    at = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                   __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), at));
+  }
+  // (each vertex is found once per pass, so the positions stay below n)
+#pragma unroll
+  for (int j = 0; j < S; ++j) {
+    if (win[j]) L.ord[at] = static_cast<uint16_t>(nb[j]);
+    at += win[j] ? 1u : 0u;
+  }
+  lds_fence();
+  return total;
+}
+
 // One level of a search: the vertices ord[fb, fe) claim their neighbours
 // and the vertices they find go to ord[fe + next, ...); returns how many.
 // LPV lanes share a vertex, each taking S of its W columns (a narrow level
@@ -269,17 +328,21 @@ __device__ EPass ell_search(const ELds& L, int32_t n, int32_t o, uint32_t root, 
   lds_fence();
   int32_t fb = o, fe = o + 1, ecc = 0;
   unsigned long long badm = 0;
+  uint32_t lowest = kFreeW;
   while (true) {
     // tokens of the level being found: (its level + 1) above lane and slot
     const uint32_t lvl = passw | static_cast<uint32_t>(ecc + 2) << kTokBits;
     const int32_t width = fe - fb;
     int32_t next;
     if (width <= 16)
-      next = ell_search_level<W / 4, 4, kCheck>(L, n, fb, fe, lvl, badm);
+      next = ell_near_level<W / 4, 4, false, kCheck>(L, fb, fe, passw, lowest);
     else if (width <= 32)
-      next = ell_search_level<W / 2, 2, kCheck>(L, n, fb, fe, lvl, badm);
+      next = ell_near_level<W / 2, 2, false, kCheck>(L, fb, fe, passw, lowest);
+    else if (width <= 64)
+      next = ell_near_level<W, 1, false, kCheck>(L, fb, fe, passw, lowest);
     else
       next = ell_search_level<W, 1, kCheck>(L, n, fb, fe, lvl, badm);
+    next = uniform(next);
     if (next == 0) break;
     fb = fe;
     fe += next;
@@ -290,7 +353,7 @@ __device__ EPass ell_search(const ELds& L, int32_t n, int32_t o, uint32_t root, 
     }
     ++ecc;
   }
-  bad |= badm != 0;
+  bad |= badm != 0 || __any(lowest == kDoneW);
   EPass r;
   r.ecc = ecc;
   r.key = ell_level_key(L, fb, fe);
@@ -380,19 +443,24 @@ template <int W>
 __device__ EPass ell_label(const ELds& L, int32_t n, int32_t o, uint32_t root, bool& bad) {
   if (threadIdx.x == 0) {
     L.ord[o] = static_cast<uint16_t>(root);
-    lds_st(&L.clm[root], static_cast<uint32_t>(o) + 1u);
+    // (below every claim of the pass, so that its row's fillers win nothing)
+    lds_st(&L.clm[root], static_cast<uint32_t>(o));
   }
   lds_fence();
   int32_t b = o, e = o + 1, levels = 1;
   while (true) {
     const int32_t width = e - b;
     int32_t placed;
+    uint32_t unused = 0;
     if (width <= 16)
-      placed = ell_label_level<W / 4, 4>(L, n, b, e);
+      placed = ell_near_level<W / 4, 4, true, false>(L, b, e, 0u, unused);
     else if (width <= 32)
-      placed = ell_label_level<W / 2, 2>(L, n, b, e);
+      placed = ell_near_level<W / 2, 2, true, false>(L, b, e, 0u, unused);
+    else if (width <= 64)
+      placed = ell_near_level<W, 1, true, false>(L, b, e, 0u, unused);
     else
       placed = ell_label_level<W, 1>(L, n, b, e);
+    placed = uniform(placed);
     if (placed == 0) break;
     if (e + placed > n) {
       bad = true;
@@ -751,7 +819,7 @@ __global__ void __launch_bounds__(kEThreads)
   // 3. the components, on the first wave
   long long t_search = 0, t_label = 0, t_rev = 0;
   EAcc acc;
-  if (tid < 64) {
+  if (uniform(tid >> 6) == 0) {  // (a scalar branch: its state stays scalar)
     acc = W == 4 ? ell_components<4>(L, J, O, n, t_search, t_label, t_rev)
                  : ell_components<8>(L, J, O, n, t_search, t_label, t_rev);
     if (tid == 0) {

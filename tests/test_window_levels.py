@@ -1,7 +1,8 @@
-"""Levels of the window engine without checks, at the widths that change how
-many lanes a vertex gets, and components whose ids reach so far that the
-window's ends allow few such levels or none.  Whole numbers throughout: every
-result must equal the oracle's."""
+"""Levels of the window engine and of the bounded-row engine that one wave
+walks without checks, at the widths that change how many lanes a vertex gets,
+and components whose ids reach so far that the window's ends allow few such
+levels or none.  Whole numbers throughout: every result must equal the
+oracle's."""
 
 import numpy as np
 import pytest
@@ -56,3 +57,21 @@ def test_far_neighbours(side):
     g = I.from_edges(n, np.concatenate(u), np.concatenate(v),
                      perm=np.random.default_rng(side).permutation(n), name=f"grid_on_path_{side}")
     _check(g)
+
+
+@pytest.mark.parametrize("width", [1, 2, 15, 16, 17, 31, 32, 33, 63, 64, 65])
+def test_small_strip_widths(width):
+    """Components in one work-group's LDS, with rows of at most 4 and of at
+    most 8 off-diagonal entries, twice (the words of the first one are not
+    free when the second is walked) and next to isolated vertices."""
+    for diagonals in (False, True):
+        m = min(2000 // width, 300)
+        i = np.arange(width * m).reshape(m, width)
+        u, v = [i[:, :-1].ravel(), i[:-1].ravel()], [i[:, 1:].ravel(), i[1:].ravel()]
+        if diagonals:
+            u += [i[:-1, :-1].ravel(), i[:-1, 1:].ravel()]
+            v += [i[1:, 1:].ravel(), i[1:, :-1].ravel()]
+        g = I.from_edges(i.size, np.concatenate(u), np.concatenate(v), name=f"strip_{width}")
+        g = I.disjoint_union([g, I.path(1), g, I.path(1)], seed=width)
+        for opts in ({}, {"pp_variant": 1, "reverse_mode": 1}, {"reverse_mode": 1}):
+            _check(g, **opts)
