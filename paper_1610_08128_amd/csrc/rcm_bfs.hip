@@ -119,6 +119,14 @@ __device__ __forceinline__ int32_t* kept_row(SharedBuf& u, int32_t i) {
 // reached the vertex, alongside its atomic.
 constexpr int kORowCap = 1024;
 
+// Labelled levels with one barrier (ordered_label_levels): parents in a
+// work-group's list, places in a list of children, the first of the keys.
+constexpr int kOrderedCap = 256;
+constexpr int kOrderedBits = 11;  // places in a list
+static_assert(kOrderedCap * kRB <= (1 << kOrderedBits) && kOrderedCap * kRB <= kStageCap,
+              "the children of a list fit a list");
+constexpr uint32_t kOrderedKeys = 0x80000000u;
+
 // Labelled levels: a parent on a row longer than a register batch ranks up
 // to kLongKids children in registers itself; one with many more on a long
 // row is placed by the whole work-group (kHeavyCap: such parents per chunk
@@ -161,7 +169,8 @@ struct Shared {
   int32_t ovf;                     // asynchronous passes: a record found no ring slot
   int32_t lown_base;               // wide labelled level: the label range of the
   int32_t lown_len;                // children this work-group placed (its list
-  int32_t lown_ok;                 // in srec), valid when it holds them all
+  int32_t lown_ok;                 // in srec), valid when it holds them all (2: and no
+                                   // work-group's has more than kOrderedCap)
   int4 heavy[kHeavyCap];           // labelled levels: parents whose many children on a
   int32_t nheavy;                  // long row the whole work-group places (label, first
   int32_t mcnt;                    // label, children); children found so far
@@ -2121,7 +2130,7 @@ __device__ __forceinline__ void global_label_level(const BfsParams& P, Team& t, 
     if (threadIdx.x == 0) {
       S.lown_base = list_base;
       S.lown_len = S.wsum[wid];
-      S.lown_ok = S.wmax <= kStageCap ? 1 : 0;
+      S.lown_ok = S.wmax > kStageCap ? 0 : (S.wmax <= kOrderedCap ? 2 : 1);
     }
     team_barrier(t, S, false);
     if (t.aborted) return;
@@ -2246,7 +2255,7 @@ __device__ __forceinline__ void global_label_level(const BfsParams& P, Team& t, 
     // each has all the counts)
     S.lown_base = list_base;
     S.lown_len = S.wsum[wid];
-    S.lown_ok = (!solo && S.wmax <= kStageCap) ? 1 : 0;
+    S.lown_ok = solo || S.wmax > kStageCap ? 0 : (S.wmax <= kOrderedCap ? 2 : 1);
   }
   team_barrier(t, S, solo);
   if (t.aborted) return;
@@ -2266,6 +2275,291 @@ __device__ __forceinline__ void global_label_level(const BfsParams& P, Team& t, 
     if (threadIdx.x == 0)
       flag_error(t.g, RCM_ERR_NOT_SYMMETRIC, 3, t.comp, 0, levels, cur_b, cur_e, end);
     done = true;
+  }
+}
+
+// Wide labelled levels with one barrier each, while every work-group's list
+// holds at most kOrderedCap parents of short rows.
+//
+// A parent's claim has to order the parents, not to be its label: the labels
+// need the counts of the work-groups before, a barrier, but the order does
+// not, since the work-groups' lists follow each other in label order.  So a
+// child found after a level's barrier claims at once with a key made of the
+// level, its work-group and its place in the list, and the next barrier both
+// completes the claims and exchanges the counts, from which the labels follow
+// for the records.  Keys are above every label and grow from level to level.
+// The claiming atomics return the words they found, which tell a parent the
+// neighbours that no earlier level holds: what is to be known of those (their
+// degrees, ids and rows) is loaded while the barrier is waited for, and only
+// their words are read again behind it.
+//
+// (Graphs with a fixed-stride row copy only: no row is longer than a batch.)
+//
+// Leaves when a list grows too long, the level is narrow or the keys run out: the level's claims are then made again by
+// label, after the words of the vertices that could be mistaken for
+// unlabelled ones (this level's and the one's before) are set below every
+// label.
+//
+// What is left of a level is memory round trips across the dies: the words
+// read again and the ranks 2.0 us, the claims 2.5, the exchange 2.2.  Measured
+// on MI355X: the 128^3 grid (352 such levels of 6,000 vertices, 128
+// work-groups) 8.25 us a level with two barriers, 6.7 with one, the call 6.35
+// -> 5.98 ms; 60 x 60 x 61 (64 work-groups) 7.1 -> 5.4 us, 2.73 -> 2.50 ms.
+// Loading the rows of the children found only behind the barrier took 7.5 and
+// 6.1; sharing the level out again every 4 or 12 levels instead of every 8,
+// 7.5 and 7.5 us (the smallest labels have most of the children, so the
+// lists drift apart quickly).
+__device__ __forceinline__ void ordered_label_levels(const BfsParams& P, Team& t, Shared& S,
+                                                     int32_t first, int32_t end, int32_t& cur_b,
+                                                     int32_t& cur_e, int32_t& levels, bool& done,
+                                                     long long& my_m, int& since,
+                                                     uint32_t& next_key) {
+  const int B = blockDim.x;
+  const int tid = threadIdx.x;
+  const int W = t.W, wid = t.wid;
+  const uint32_t step = static_cast<uint32_t>(W) << kOrderedBits;
+  int4* list = reinterpret_cast<int4*>(S.u.srec);
+  // the level's own list: records, claimed with first_key + place
+  int32_t len = S.lown_len, base = S.lown_base;
+  uint32_t first_key = static_cast<uint32_t>(base);
+  uint32_t level_key = 0;  // work-group 0's first key, of a level found here
+  bool entered = true;  // nothing of the list is in registers yet
+  int32_t u = -1;       // this thread's parent, its row,
+  int32_t nb[kRB];
+  // the first kKids of its neighbours that no earlier level holds (their
+  // degrees, ids and rows are loaded while the barrier is waited for), and
+  // which others are none either
+  constexpr int kKids = 3;
+  int kids = 0;
+  unsigned others = 0;
+  int32_t kid[kKids];
+  int4 kinf[kKids], krow[kKids][2];
+  // the first kKids of the neighbours in `mask` with what is known of them
+  // (past the last: the last one's again), the rest to `others`
+  auto keep = [&](unsigned mask) {
+    kids = __popc(mask) < kKids ? __popc(mask) : kKids;
+    others = 0;
+    if (mask == 0) return;
+    unsigned left = mask;
+#pragma unroll
+    for (int q = 0; q < kKids; ++q) {
+      const int at = __ffs(static_cast<int>(left)) - 1;
+      kid[q] = nb[0];
+#pragma unroll
+      for (int j = 1; j < kRB; ++j) kid[q] = at == j ? nb[j] : kid[q];
+      const unsigned rest = left & (left - 1u);
+      if (q == kKids - 1) others = rest;
+      left = rest != 0 ? rest : left;
+    }
+    if (__popc(mask) <= kKids) others = 0;
+#pragma unroll
+    for (int q = 0; q < kKids; ++q) {
+      kinf[q] = P.vinfo[kid[q]];
+      krow[q][0] = P.ell[2 * static_cast<size_t>(kid[q])];
+      krow[q][1] = P.ell[2 * static_cast<size_t>(kid[q]) + 1];
+    }
+  };
+  while (true) {
+    const long long ta = wall_clock64();
+    bool act = tid < len;
+    uint32_t mine = first_key + static_cast<uint32_t>(tid);
+    const bool even = since % P.rebalance == 0;
+    if (even) {
+      // the level in even chunks, read back from the records: the place of
+      // each parent in its old list gives its key
+      int tot;
+      const int before = block_excl_scan(tid < W ? S.wsum[tid] : 0, S.scan, &tot);
+      __syncthreads();
+      if (tid < W) S.wsum[tid] = before;
+      int32_t lo, hi;
+      my_chunk(cur_b, cur_e, W, wid, lo, hi);
+      __syncthreads();
+      int32_t a = 0, p = lo + tid;
+      act = p < hi;
+      if (act) {
+        // the last work-group that starts at or before the parent's place
+        const int32_t at = p - cur_b;
+        for (int32_t d = kMaxTeam / 2; d > 0; d >>= 1)
+          if (a + d < W && S.wsum[a + d] <= at) a += d;
+        mine = level_key + (static_cast<uint32_t>(a) << kOrderedBits) +
+               static_cast<uint32_t>(at - S.wsum[a]);
+      }
+      team_barrier(t, S, false);  // (the records)
+      if (t.aborted) return;
+      u = -1;
+      if (act) {
+        u = ld_rec(P, p).x;
+        ell_row(P.ell, u, nb);
+      }
+    } else if (entered && act) {
+      u = list[tid].x;
+      const int32_t* kr = kept_row(S.u, tid);
+#pragma unroll
+      for (int j = 0; j < kRB; ++j) nb[j] = kr[j] & 0x7fffffff;
+    }
+    // children: the neighbours that hold this parent's key
+    unsigned is_kid = 0;
+    if (even || entered) {
+      unsigned mask = 0;
+      if (act) {
+        uint32_t cl[kRB];
+#pragma unroll
+        for (int j = 0; j < kRB; ++j) cl[j] = ld_relaxed(&P.claim[nb[j]]);
+#pragma unroll
+        for (int j = 0; j < kRB; ++j) mask |= (nb[j] != u && cl[j] == mine ? 1u : 0u) << j;
+      }
+      keep(mask);
+      is_kid = (1u << kids) - 1u;
+    } else if (kids > 0) {
+      uint32_t cl[kKids];
+#pragma unroll
+      for (int q = 0; q < kKids; ++q) cl[q] = ld_relaxed(&P.claim[kid[q]]);
+#pragma unroll
+      for (int q = 0; q < kKids; ++q) is_kid |= (q < kids && cl[q] == mine ? 1u : 0u) << q;
+      if (others != 0) {
+        unsigned found = 0;
+#pragma unroll
+        for (int j = 0; j < kRB; ++j)
+          if (others >> j & 1u) found |= (ld_relaxed(&P.claim[nb[j]]) == mine ? 1u : 0u) << j;
+        others = found;
+      }
+    }
+    int tot;
+    const int ex = block_excl_scan(__popc(is_kid) + __popc(others), S.scan, &tot);
+    if (is_kid != 0 || others != 0) {
+      // ranked by (degree, id) into the list, their rows behind it
+      uint64_t key[kKids], more[kRB];
+#pragma unroll
+      for (int q = 0; q < kKids; ++q)
+        key[q] = (is_kid >> q & 1u) ? pack_key(kinf[q].z, kinf[q].w) : kMaxKey;
+      if (others != 0) {
+#pragma unroll
+        for (int j = 0; j < kRB; ++j) {
+          more[j] = kMaxKey;
+          if (!(others >> j & 1u)) continue;
+          const int4 inf = P.vinfo[nb[j]];
+          more[j] = pack_key(inf.z, inf.w);
+        }
+      }
+      auto place = [&](uint64_t k, int32_t v, int4 inf, int4 lo, int4 hi) {
+        int at = ex;
+#pragma unroll
+        for (int q = 0; q < kKids; ++q) at += key[q] < k ? 1 : 0;
+        if (others != 0) {
+#pragma unroll
+          for (int j = 0; j < kRB; ++j) at += more[j] < k ? 1 : 0;
+        }
+        list[at] = record(v, inf);
+        my_m += inf.z;
+        if (at < kRowCap) {
+          int4* kr = reinterpret_cast<int4*>(kept_row(S.u, at));
+          kr[0] = lo;
+          kr[1] = hi;
+        }
+      };
+#pragma unroll
+      for (int q = 0; q < kKids; ++q)
+        if (is_kid >> q & 1u) place(key[q], kid[q], kinf[q], krow[q][0], krow[q][1]);
+      if (others != 0) {
+#pragma unroll
+        for (int j = 0; j < kRB; ++j) {
+          if (!(others >> j & 1u)) continue;
+          const int4* e = P.ell + 2 * static_cast<size_t>(nb[j]);
+          place(more[j], nb[j], P.vinfo[nb[j]], e[0], e[1]);
+        }
+      }
+    }
+    const int32_t last_u = u;
+    __syncthreads();
+    const long long tb = wall_clock64();
+    // Their claims, each by the thread whose parent it is at the next level.
+    // The words as they were tell the neighbours of earlier levels from those
+    // of the next.
+    first_key = next_key + (static_cast<uint32_t>(wid) << kOrderedBits);
+    u = -1;
+    unsigned mask = 0;
+    if (tid < tot) {
+      u = list[tid].x;
+      const int32_t* kr = kept_row(S.u, tid);
+#pragma unroll
+      for (int j = 0; j < kRB; ++j) nb[j] = kr[j];
+      uint32_t old[kRB];
+#pragma unroll
+      for (int j = 0; j < kRB; ++j) {
+        old[j] = 0;
+        if (nb[j] != u)
+          old[j] = atomicMin(&P.claim[nb[j]], first_key + static_cast<uint32_t>(tid));
+      }
+#pragma unroll
+      for (int j = 0; j < kRB; ++j) mask |= (old[j] >= next_key ? 1u : 0u) << j;
+    }
+    for (int32_t k = tid + B; k < tot; k += B) {
+      const int32_t v = list[k].x;
+      int32_t row[kRB];
+      ell_row(P.ell, v, row);
+#pragma unroll
+      for (int j = 0; j < kRB; ++j)
+        if (row[j] != v) atomicMin(&P.claim[row[j]], first_key + static_cast<uint32_t>(k));
+    }
+    drain_memory_ops();
+    keep(mask);
+    entered = false;
+    const long long tc = wall_clock64();
+    slot_exchange(t, S, static_cast<uint32_t>(tot), false);
+    if (t.aborted) return;
+    if (wid == 0 && tid == 0) {
+      const long long td = wall_clock64();
+      t.ctl->clk[12] += td - ta;
+      t.ctl->clk[13] += 1;
+      t.ctl->clk[16] += tb - ta;
+      t.ctl->clk[18] += tc - tb;
+      t.ctl->clk[19] += td - tc;
+      t.ctl->clk[30] += 1;  // levels that took this path
+    }
+    const int32_t total = S.wtot, widest = S.wmax;
+    level_key = next_key;
+    next_key += step;
+    if (total == 0) {
+      done = true;
+      return;
+    }
+    len = tot;
+    base = cur_e + S.wpre;
+    cur_b = cur_e;
+    cur_e += total;
+    ++levels;
+    ++since;
+    if (cur_e > end) {
+      if (tid == 0)
+        flag_error(t.g, RCM_ERR_NOT_SYMMETRIC, 3, t.comp, 0, levels, cur_b, cur_e, end);
+      done = true;
+      return;
+    }
+    for (int32_t k = tid; k < len; k += B) st_rec(&P.qi[base + k], list[k]);
+    if (widest <= kOrderedCap && total >= P.narrow_cutoff &&
+        next_key < 0xFFFFFFFFu - 2 * step)
+      continue;
+    // back to claims by label
+    auto below = [&](int32_t v) {
+      __hip_atomic_store(&P.claim[v], static_cast<uint32_t>(first), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (last_u >= 0) below(last_u);
+    for (int32_t k = tid; k < len; k += B) below(list[k].x);
+    team_barrier(t, S, false);
+    if (t.aborted) return;
+    for (int32_t k = tid; k < len; k += B) {
+      int32_t row[kRB];
+      ell_row(P.ell, list[k].x, row);
+      claim_batch(P, row, static_cast<uint32_t>(base + k));
+    }
+    if (tid == 0) {
+      S.lown_base = base;
+      S.lown_len = len;
+      S.lown_ok = 1;
+    }
+    team_barrier(t, S, false);
+    return;
   }
 }
 
@@ -2295,6 +2589,7 @@ __device__ __forceinline__ int32_t label_pass(const BfsParams& P, Team& t, Share
   if (t.aborted) return 0;
   int32_t cur_b = o, cur_e = o + 1, levels = 1;
   long long my_m = (t.wid == 0 && threadIdx.x == 0) ? rinf.z : 0;
+  uint32_t next_key = kOrderedKeys;
   bool done = false;
   while (!done) {
     const bool narrow = t.W > 1 && (cur_e - cur_b) < P.narrow_cutoff;
@@ -2328,9 +2623,20 @@ __device__ __forceinline__ int32_t label_pass(const BfsParams& P, Team& t, Share
     }
     // wide levels; every `rebalance` levels the parents are chunked evenly
     // again instead of taken from each work-group's own list
-    for (int since = 0; !done && (cur_e - cur_b) >= P.narrow_cutoff; ++since) {
-      global_label_level(P, t, S, end, false, cur_b, cur_e, levels, done, my_m,
-                         since % P.rebalance != 0);
+    // (two levels at least by label first: the lists come from the second)
+    int since = 0;
+    bool listed = false;  // the last level left every work-group's list
+    while (!done && (cur_e - cur_b) >= P.narrow_cutoff) {
+      if (listed && P.ell != nullptr && since % P.rebalance != 0 &&
+          next_key < 0xFFFFFFFFu - 2 * (static_cast<uint32_t>(t.W) << kOrderedBits)) {
+        ordered_label_levels(P, t, S, o, end, cur_b, cur_e, levels, done, my_m, since, next_key);
+        listed = false;
+      } else {
+        global_label_level(P, t, S, end, false, cur_b, cur_e, levels, done, my_m,
+                           since % P.rebalance != 0);
+        ++since;
+        listed = S.lown_ok == 2;
+      }
       if (t.aborted) return 0;
     }
   }
