@@ -251,6 +251,9 @@ constexpr int32_t kHeadWidth = kComponentEllCap;
 constexpr int kCountsAt = 17;  // declined tasks of the component engine, three lists
 constexpr int kProbeAt = 24;   // its probe
 constexpr int kMiscInts = 28;  // what one readback covers
+// Past the component engine's range: levels from which vertex 0's component is
+// renumbered after its first structure.
+constexpr int32_t kLongLevels = 256;
 // Declined components of more vertices than this go to teams.
 constexpr int32_t kDeclinedCutoff = 1 << 14;
 
@@ -428,10 +431,18 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
                                     : 0;
   unsigned long long* dkey = reinterpret_cast<unsigned long long*>(ws + L.dkey);
   if (head) setup.put(seeds, int32_t{0});
-  if (head && component && renumber_from > 0) setup.fill(dkey, 8 * N, 0);
+  // A graph too large for the engine may still hold a long component, whose
+  // first structure one work-group walks faster than a team (a strip of 32 x
+  // 31,250 vertices under random labels: 28.2 -> 13.9 ms, 1.65 and 0.82 us a
+  // level); it is renumbered from there.  A surface or a volume is left to
+  // the team within some 64 and 8 levels.
+  const bool short_rows = static_cast<int64_t>(g.nnz) <= 8 * static_cast<int64_t>(g.n);
+  const bool long_probe = head && opt.component && !component && g.n <= kLongRange &&
+                          renumber_from > 0 && window_enabled() && short_rows &&
+                          ell != nullptr && ell_enabled();
+  if (head && (component || long_probe) && renumber_from > 0) setup.fill(dkey, 8 * N, 0);
   HIP_TRY(launch_setup(&setup, s));
   HIP_TRY(launch_validate_scan(g, vinfo, beta, segstats, misc + 0, misc + 3, ell, misc + 6, s));
-  const bool short_rows = static_cast<int64_t>(g.nnz) <= 8 * static_cast<int64_t>(g.n);
   ComponentParams C{};
   C.n = g.n;
   C.colidx = g.colidx;
@@ -457,7 +468,7 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
   // components only has to cover the vertices it did not reach.  (Single
   // graphs only; a batch runs the search over every graph.)
   const int32_t head_anchor = opt.reverse_mode == 1 ? g.n - 1 : -1;
-  if (head && component) {
+  if (head && (component || long_probe)) {
     // The component engine's probe of it, right behind the scan, whose
     // verdict the probe reads on the device: the readback below covers both.
     ComponentParams probe = C;
@@ -474,16 +485,19 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
                    : short_rows                                                       ? 28
                                                                                       : 32;
     timer.kmark(1, true);
-    HIP_TRY(launch_component(probe, s));
+    HIP_TRY(long_probe ? launch_long_probe(probe, s) : launch_component(probe, s));
     timer.kmark(1, false);
   }
   int32_t h[kMiscInts];
   rcm_status st = read_ints(h, misc, kMiscInts, s);
   if (st != RCM_OK) return st;
   if (h[0]) return RCM_ERR_BAD_CSR;
-  const bool probed = head && component && h[kCountsAt] == 0;
   ComponentProbe pr{};
   std::memcpy(&pr, h + kProbeAt, sizeof(pr));
+  // (a component of a few levels is not worth a renumbering: past the
+  // engine's range the team kernel walks it again)
+  const bool probed = head && h[kCountsAt] == 0 &&
+                      (component || (long_probe && pr.ecc + 1 >= kLongLevels));
   // a row longer than the copy's width: the team kernel reads the CSR (the
   // component engine decides that for each component)
   if (h[6] || !ell_enabled()) ell = nullptr;
@@ -546,7 +560,7 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
     setup.fill(claim, 4 * N, -1);
     if (opt.async_search) setup.fill(P.dkey, 8 * N, 0);
   };
-  if (!component) {
+  if (!component && !(probed && long_probe)) {
     ready_team();
     // (a batch's isolated vertices write their keys before the launch)
     if (!head) HIP_TRY(launch_setup(&setup, s));
@@ -652,7 +666,7 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
     g_used[5] = opt.small_cutoff;
   };
   int32_t head_size = 0;
-  if (head && component) {
+  if (head && (component || long_probe)) {
     note_settings();
     if (opt.abort_flag) {
       int32_t err = 0;
@@ -666,7 +680,9 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
   }
   // the probed component is a long one: renumbered below for the window engine
   const bool probed_long = probed && renumber_from > 0 && window_enabled() &&
-                           pr.ecc + 1 >= renumber_from;
+                           (long_probe || pr.ecc + 1 >= renumber_from);
+  // (what the window engine declines of it, a team takes up)
+  const bool team_resumes = !probed || long_probe;
   bool head_done = !probed;  // ordered completely
   if (head && (!probed || probed_long)) {
     const CompTask ht{0, -1, 0, 0, head_anchor};
@@ -765,12 +781,17 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
         windowed = wst == 0;
         // declined: the team kernel's distance words start below every pass
         // tag again
-        if (!windowed && !probed)
+        if (!windowed && team_resumes)
           HIP_TRY(hipMemsetAsync(P.dkey, 0, 8 * static_cast<size_t>(g.n), s));
       }
-      if (!windowed && !probed) {
+      if (!windowed && team_resumes) {
         long long clk_first[32];
         std::memcpy(clk_first, timer.clk, sizeof(clk_first));
+        if (probed) {
+          setup.fill(claim, 4 * N, -1);
+          setup.put(&gctl->p1_ecc, ecc1);
+          setup.put(&gctl->p1_lastkey, pr.key);
+        }
         const CompTask rt{0, size1, 0, 0, ht.anchor};
         setup.put(t_big, rt);
         int32_t* visit2 = csize;  // free again once the renumbering is built
@@ -799,8 +820,8 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
       // the other components claim in the caller's numbering from scratch
       if (size1 < g.n && team_ready) HIP_TRY(hipMemsetAsync(claim, 0xFF, 4 * N, s));
       // the window engine / the team kernel, renumbered
-      if (windowed || !probed) g_used[0] = windowed ? 4 : 3;
-      head_done = windowed || !probed;
+      if (windowed || team_resumes) g_used[0] = windowed ? 4 : 3;
+      head_done = windowed || team_resumes;
     }
     if (head_done) head_size = hres[4];
     if (head_size < 1 || head_size > g.n) return RCM_ERR_HIP;
@@ -814,6 +835,7 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
     const CompTask* small = t_small;
     int32_t left[3] = {0, n_big, n_small};
     if (component) note_settings();
+    else ready_team();
     if (component && (n_big + n_small > 0 || !head_done)) {
       if (!head_done) {
         C.head = CompTask{0, head_size, 0, 0, head_anchor >= 0 ? head_anchor : head_size - 1};

@@ -588,6 +588,11 @@ struct ComponentParams {
   const int32_t* abort_flag;   // the caller's abort flag, or null
 };
 hipError_t launch_component(const ComponentParams& p, hipStream_t s);
+// The first level structure of vertex 0's component alone (dkey, visit and
+// probe as above), for a graph of up to kLongRange vertices with a row copy;
+// counts[0] is raised when its levels are wider than a long component's.
+constexpr int32_t kLongRange = 1146880;
+hipError_t launch_long_probe(const ComponentParams& p, hipStream_t s);
 // The declined tasks, in list order: the head and the large ones, the small
 // ones.
 hipError_t launch_declined(const ComponentParams& p, CompTask* big_out, CompTask* small_out,

@@ -1021,6 +1021,172 @@ __global__ void __launch_bounds__(kThreads) k_component(ComponentParams P) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// The first level structure of a long component of a graph too large for the
+// engine above: levels of at most kLongCap vertices of bounded rows, visited
+// marks of at most kLongRange vertices.  It only measures, so its LDS holds
+// the marks and two levels of rows, and nothing else.  A level is one memory
+// round trip, the rows of the vertices found (0.82 us for the strip of 32 x
+// 31,250 vertices, whose rows no die's L2 holds; the team took 1.65).  Loads
+// of the next level's rows ahead of the barrier made it 1.29 us: the loads
+// behind them wait for them.
+// ---------------------------------------------------------------------------
+constexpr int kLongThreads = 512;
+constexpr int kLongCap = 256;
+struct LongLds {
+  uint32_t bits[kLongRange / 32];
+  int4 row[2][kLongCap][2];
+  int32_t v[2][kLongCap];
+  int32_t cnt[3];
+  int32_t stop;
+  unsigned long long key;
+};
+static_assert(sizeof(LongLds) <= 160 * 1024, "one work-group's LDS");
+
+// x added to *p by one lane (the compiler would wrap a plain atomic of one
+// lane in a second reduction over the wave).
+__device__ __forceinline__ int32_t lds_add(int32_t* p, int32_t x) {
+  const uint32_t at = static_cast<uint32_t>(
+      reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) int32_t*)p));
+  int32_t old;
+  asm volatile("ds_add_rtn_u32 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(old)
+               : "v"(at), "v"(x)
+               : "memory");
+  return old;
+}
+
+// kN entries a lane of the rows of the level's vertices: the new ones, with
+// their rows, to the next level.  (A row's own vertex and its fillers are
+// marked already.)
+template <int kN>
+__device__ __forceinline__ void long_reach(const ComponentParams& P, LongLds& S, int b,
+                                           int32_t len, int32_t level, int32_t* cnt) {
+  constexpr int kLanes = kEllWidth / kN;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int32_t i = tid / kLanes;
+  if (i >= len) return;
+  const int32_t* mine = reinterpret_cast<const int32_t*>(S.row[b][i]) + kN * (tid % kLanes);
+  int32_t w[kN], r[kN][kEllWidth];
+  uint32_t old[kN];
+  bool fresh[kN];
+#pragma unroll
+  for (int j = 0; j < kN; ++j) w[j] = mine[j];
+#pragma unroll
+  for (int j = 0; j < kN; ++j)
+    old[j] = atomicOr(&S.bits[static_cast<uint32_t>(w[j]) >> 5], bit_of(static_cast<uint32_t>(w[j])));
+#pragma unroll
+  for (int j = 0; j < kN; ++j) {
+    fresh[j] = (old[j] & bit_of(static_cast<uint32_t>(w[j]))) == 0;
+    const int4* row = P.ell + 2 * static_cast<size_t>(fresh[j] ? w[j] : 0);
+    const int4 lo = row[0], hi = row[1];
+    r[j][0] = lo.x; r[j][1] = lo.y; r[j][2] = lo.z; r[j][3] = lo.w;
+    r[j][4] = hi.x; r[j][5] = hi.y; r[j][6] = hi.z; r[j][7] = hi.w;
+  }
+  // (behind the loads, which would otherwise wait for the stores)
+#pragma unroll
+  for (int j = 0; j < kN; ++j)
+    if (fresh[j]) P.dkey[w[j]] = distance_word(level + 1);
+  int total = 0;
+  unsigned long long m[kN], all = 0;
+#pragma unroll
+  for (int j = 0; j < kN; ++j) {
+    m[j] = __ballot(fresh[j]);
+    total += __popcll(m[j]);
+    all |= m[j];
+  }
+  if (all == 0) return;
+  const int first = __builtin_ctzll(all);
+  int base = 0;
+  if (lane == first) base = lds_add(cnt, total);
+  base = __builtin_amdgcn_readlane(base, first);
+#pragma unroll
+  for (int j = 0; j < kN; ++j) {
+    const int at = base + __builtin_amdgcn_mbcnt_hi(
+                              static_cast<uint32_t>(m[j] >> 32),
+                              __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m[j]), 0));
+    base += __popcll(m[j]);
+    if (!fresh[j] || at >= kLongCap) continue;
+    S.v[b ^ 1][at] = w[j];
+    S.row[b ^ 1][at][0] = make_int4(r[j][0], r[j][1], r[j][2], r[j][3]);
+    S.row[b ^ 1][at][1] = make_int4(r[j][4], r[j][5], r[j][6], r[j][7]);
+    if (r[j][0] < 0) atomicAdd(cnt, kLongRow);
+  }
+}
+
+__global__ void __launch_bounds__(kLongThreads) k_long_probe(ComponentParams P) {
+  __shared__ LongLds S;
+  if (ld_relaxed(P.bad_csr) != 0) return;
+  const int tid = threadIdx.x;
+  for (int32_t i = tid; i < (P.n + 31) / 32; i += kLongThreads) S.bits[i] = 0;
+  if (tid < 3) S.cnt[tid] = 0;
+  __syncthreads();
+  if (tid == 0) {
+    const int4 lo = P.ell[0];
+    S.v[0][0] = 0;
+    S.row[0][0][0] = lo;
+    S.row[0][0][1] = P.ell[1];
+    S.bits[0] = 1;
+    S.key = kMaxKey;
+    P.dkey[0] = distance_word(0);
+    S.stop = lo.x < 0 ? 1 : 0;
+  }
+  __syncthreads();
+  bool decline = uniform(S.stop) != 0;
+  int32_t len = 1, total = 1, level = 0, near = 0;
+  int l3 = 0;
+  while (!decline) {
+    int32_t* cnt = &S.cnt[l3];
+    l3 = l3 == 2 ? 0 : l3 + 1;
+    if (tid == 0) S.cnt[l3] = 0;
+    const int b = level & 1;
+    if (len <= kLongThreads / 8)
+      long_reach<1>(P, S, b, len, level, cnt);
+    else if (len <= kLongThreads / 4)
+      long_reach<2>(P, S, b, len, level, cnt);
+    else
+      long_reach<4>(P, S, b, len, level, cnt);
+    __syncthreads();
+    const int32_t found = uniform(*cnt);
+    if (found == 0) break;
+    // (a level that grows like a volume's: see component_pass)
+    if (level == 3) near = found;
+    decline = found > kLongCap || (level == 7 && found * 10 >= near * P.growth);
+    total += found;
+    len = found;
+    ++level;
+    if (P.abort_flag != nullptr && (level & 63) == 0) {
+      if (tid == 0) {
+        S.stop = abort_requested(P.abort_flag) ? 1 : 0;
+        if (S.stop != 0) flag_error(P.gctl, RCM_ERR_ABORTED);
+      }
+      __syncthreads();
+      if (uniform(S.stop) != 0) return;
+      __syncthreads();
+    }
+  }
+  if (decline) {
+    if (tid == 0) atomicAdd(&P.counts[0], 1);
+    return;
+  }
+  // the minimum (degree, id) of the last level
+  if (tid < len) {
+    const int32_t v = S.v[level & 1][tid];
+    const int4 lo = S.row[level & 1][tid][0], hi = S.row[level & 1][tid][1];
+    atomicMin(&S.key, static_cast<unsigned long long>(
+                          pack_key(EllLevels::degree(v, lo, hi), v)));
+  }
+  __syncthreads();
+  if (tid == 0) {
+    P.probe->ecc = level;
+    P.probe->size = total;
+    P.probe->key = S.key;
+  }
+  if (total != P.n)
+    for (int32_t i = tid; i < P.n; i += kLongThreads)
+      P.visit[i] = static_cast<int32_t>(S.bits[i >> 5] >> (i & 31) & 1u);
+}
+
 // The declined tasks, in list order (vertex 0's component and the large ones,
 // then the small ones), for the team kernel: one work-group.
 __global__ void __launch_bounds__(kThreads)
@@ -1052,6 +1218,11 @@ hipError_t launch_component(const ComponentParams& p, hipStream_t s) {
   // a work-group's LDS leaves room for one per CU; more would only queue
   const int blocks = static_cast<int>(tasks < 1024 ? tasks : 1024);
   k_component<<<blocks, kThreads, 0, s>>>(p);
+  return hipGetLastError();
+}
+
+hipError_t launch_long_probe(const ComponentParams& p, hipStream_t s) {
+  k_long_probe<<<1, kLongThreads, 0, s>>>(p);
   return hipGetLastError();
 }
 
