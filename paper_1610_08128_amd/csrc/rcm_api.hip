@@ -1208,27 +1208,34 @@ bool order_small(int32_t n, const int32_t* rowptr, const int32_t* colidx, int32_
   };
   timer.mark(0);
   timer.kmark(0, true);
-  // the bounded-row engine first where the graph can fit it; it declines
-  // graphs with longer rows, which the general engine then takes
-  const bool try_ell = small_ell_enabled() && small_ell_lds_bytes(n) <= limit;
-  bool ok = true;
+  // The bounded-row engine first where the graph can fit it; it declines
+  // graphs with longer rows.
+  // A graph with a long row, or of more vertices than that engine's records
+  // fit: 16 waves, several lanes a row, wherever they fit (mean rows of 12,
+  // 500 / 2,000 / 4,000 vertices: 391 -> 103, 1,228 -> 191, 2,201 -> 301 us;
+  // of 5, 3,000 vertices: 832 -> 234; a band of 4,000 whose levels are 4 wide:
+  // 10.0 -> 3.6 ms; the 80 x 80 grid, too large for the records: 1,300 -> 491).
+  // Only the smallest graphs of short rows keep the one wave, and the block
+  // threads they have always reported (166 vertices, mean row 5: 216 against
+  // 104 us).
+  const bool ell_on = small_ell_enabled();
+  const bool try_ell = ell_on && small_ell_lds_bytes(n) <= limit;
+  bool ok = true, declined = true;
   if (try_ell) {
     ok = run_kernel(kBoundedRows);
     g_used[2] = 512;
+    declined = h.status == kSmallDeclined;
+    if (declined) job.nnz = h.nnz;
   }
-  if (ok && (!try_ell || h.status == kSmallDeclined)) {
-    // A graph with a long row: 16 waves, several lanes a row, wherever they
-    // fit (mean rows of 12, 500 / 2,000 / 4,000 vertices: 391 -> 103, 1,228 ->
-    // 191, 2,201 -> 301 us; of 5, 3,000 vertices: 832 -> 234; a band of 4,000
-    // whose levels are 4 wide: 10.0 -> 3.6 ms).  Only the smallest graphs of
-    // short rows keep the one wave, and the block threads they have always
-    // reported (166 vertices, mean row 5: 216 against 104 us).  Where the
-    // bounded-row engine was not asked, the entry count is not known here.
-    const bool wide = try_ell && (n >= 256 || h.nnz > 8 * static_cast<int64_t>(n)) &&
-                      small_wide_lds_bytes(n, h.nnz) <= limit;
-    if (wide) job.nnz = h.nnz;
-    ok = run_kernel(wide ? kLongRows : kGeneral);
-    g_used[2] = wide ? 1024 : 64;
+  if (ok && declined && ell_on && (n >= 256 || job.nnz > 8 * static_cast<int64_t>(n)) &&
+      small_wide_lds_bytes(n, job.nnz < 0 ? 0 : job.nnz) <= limit) {
+    ok = run_kernel(kLongRows);
+    g_used[2] = 1024;
+    declined = h.status == kSmallDeclined;
+  }
+  if (ok && declined) {
+    ok = run_kernel(kGeneral);
+    g_used[2] = 64;
   }
   if (!ok) *out = RCM_ERR_HIP;
   timer.kmark(0, false);

@@ -515,9 +515,9 @@ hipError_t launch_window_order(const WinParams& P, hipStream_t s);
 size_t small_ell_lds_bytes(int64_t n);
 hipError_t launch_small_ell(const SmallJob& job, const SmallOpts& opts, hipStream_t s);
 
-// The 16-wave variant for long rows (rcm_small_wide.hip) for one graph whose
-// entry count the host knows (job.nnz): LDS bytes it needs (SIZE_MAX outside
-// its sizes) and its launch.
+// The 16-wave variant (rcm_small_wide.hip) for one graph: LDS bytes it needs
+// (SIZE_MAX outside its sizes) and its launch.  With job.nnz < 0 it reads the
+// entry count itself, and declines a graph that does not fit.
 size_t small_wide_lds_bytes(int64_t n, int64_t nnz);
 hipError_t launch_small_wide(const SmallJob& job, const SmallOpts& opts, hipStream_t s);
 

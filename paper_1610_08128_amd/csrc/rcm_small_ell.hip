@@ -20,12 +20,15 @@
 //   (on levels wider than the wave the claim is a (level, lane, slot) token
 //   instead, found back by its own lane).  A level is then three dependent
 //   LDS round trips: its queue entries, their rows, the claims.
-// - A level of at most 64 vertices, which is what such graphs mostly have,
-//   takes one pass of the wave without a test per column (ell_near_level),
-//   and what the level loops keep is scalar: both are a third of the
-//   instructions, which is what a level's time was (the 64 x 64 grid: 0.45
-//   us a search level and 0.40 a labelled one before, 0.30 and 0.29 now;
-//   the call 218 -> 164 us, the 32 x 32 grid's 92 -> 76).
+// - A level of at most 64 vertices (128 where rows hold at most 4), which is
+//   what such graphs mostly have, is in the wave's registers and takes no
+//   test per column (ell_near_level), and what the level loops keep is
+//   scalar: both are a third of the instructions, which is what a level's
+//   time was (the 64 x 64 grid: 0.45 us a search level and 0.40 a labelled
+//   one before, 0.27 and 0.28 now; the call 216 -> 154 us, the 32 x 32
+//   grid's 93 -> 75).  Forms for 256 vertices, or for 128 with rows of 8,
+//   took every level twice as long: the kernel then needs 248 registers and
+//   87 KB of code.
 // - The bulk phases (loading with the checks, the row sort, the statistics
 //   of the result) run on eight waves; the level loops, whose levels are a
 //   wave wide on such graphs, run on the first wave alone while the others
@@ -185,52 +188,67 @@ __device__ __forceinline__ uint32_t ell_level_key(const ELds& L, int32_t b, int3
 // A value that is the same in every lane, as a scalar.
 __device__ __forceinline__ int32_t uniform(int32_t x) { return __builtin_amdgcn_readfirstlane(x); }
 
-// One level of at most 64 / LPV vertices ord[b, e), either kind of pass: lanes
-// past the level stand for its last vertex.  A search marks with the least
-// word of its pass, and the lane that finds a word above the pass's finds the
-// vertex; in the labelled BFS the lanes read their claims back, and a lane
-// past the level never holds the least label.  A row's fillers name its own
-// vertex, whose word is below either.  Returns the vertices placed.
-template <int S, int LPV, bool kLabel, bool kCheck>
+// One level of at most kChunks * 64 / LPV vertices ord[b, e), either kind of
+// pass, every chunk in registers: lanes past the level stand for its last
+// vertex.  A search marks with the least word of its pass, and the lane that
+// finds a word above the pass's finds the vertex; in the labelled BFS the
+// lanes read their claims back, and a lane past the level never holds the
+// least label.  A row's fillers name its own vertex, whose word is below
+// either.  Returns the vertices placed.
+template <int S, int LPV, int kChunks, bool kLabel, bool kCheck>
 __device__ __forceinline__ int32_t ell_near_level(const ELds& L, int32_t b, int32_t e,
                                                   uint32_t passw, uint32_t& lowest) {
-  const int32_t i = b + static_cast<int32_t>(threadIdx.x) / LPV;
-  const uint32_t u = L.ord[i < e ? i : e - 1];
-  uint32_t nb[S];
-  load_part<S>(L, u, threadIdx.x % LPV, nb);
-  bool win[S];
-  if (kLabel) {
-    const uint32_t mine = static_cast<uint32_t>(i) + 1u;
+  constexpr int kN = S * kChunks;
+  const int32_t i0 = b + static_cast<int32_t>(threadIdx.x) / LPV;
+  uint32_t nb[kN];
+  bool win[kN];
 #pragma unroll
-    for (int j = 0; j < S; ++j) atomicMin(&L.clm[nb[j]], mine);
+  for (int c = 0; c < kChunks; ++c) {
+    const int32_t i = i0 + c * (64 / LPV);
+    const uint32_t u = L.ord[i < e ? i : e - 1];
+    load_part<S>(L, u, threadIdx.x % LPV, nb + c * S);
+  }
+  if (kLabel) {
+    const uint32_t mine = static_cast<uint32_t>(i0) + 1u;
+#pragma unroll
+    for (int j = 0; j < kN; ++j) atomicMin(&L.clm[nb[j]], mine + j / S * (64 / LPV));
     lds_fence();
 #pragma unroll
-    for (int j = 0; j < S; ++j) win[j] = lds_ld(&L.clm[nb[j]]) == mine;
+    for (int j = 0; j < kN; ++j) win[j] = lds_ld(&L.clm[nb[j]]) == mine + j / S * (64 / LPV);
   } else {
     const uint32_t top = passw | ((1u << kPassShift) - 1u);
-    uint32_t old[S];
+    uint32_t old[kN];
 #pragma unroll
-    for (int j = 0; j < S; ++j) old[j] = atomicMin(&L.clm[nb[j]], passw);
+    for (int j = 0; j < kN; ++j) old[j] = atomicMin(&L.clm[nb[j]], passw);
 #pragma unroll
-    for (int j = 0; j < S; ++j) {
+    for (int j = 0; j < kN; ++j) {
       win[j] = old[j] > top;
       if (kCheck) lowest = old[j] < lowest ? old[j] : lowest;
     }
   }
   int32_t total = 0;
-  uint32_t at = static_cast<uint32_t>(e);
+  uint32_t at[kChunks];
 #pragma unroll
-  for (int j = 0; j < S; ++j) {
-    const unsigned long long m = __ballot(win[j]);
-    total += __popcll(m);
-    at = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
-                                   __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), at));
+  for (int c = 0; c < kChunks; ++c) {
+    at[c] = static_cast<uint32_t>(e + total);
+#pragma unroll
+    for (int j = c * S; j < (c + 1) * S; ++j) {
+      const unsigned long long m = __ballot(win[j]);
+      total += __popcll(m);
+      at[c] = __builtin_amdgcn_mbcnt_hi(
+          static_cast<uint32_t>(m >> 32),
+          __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), at[c]));
+    }
   }
   // (each vertex is found once per pass, so the positions stay below n)
 #pragma unroll
-  for (int j = 0; j < S; ++j) {
-    if (win[j]) L.ord[at] = static_cast<uint16_t>(nb[j]);
-    at += win[j] ? 1u : 0u;
+  for (int c = 0; c < kChunks; ++c) {
+    uint32_t to = at[c];
+#pragma unroll
+    for (int j = c * S; j < (c + 1) * S; ++j) {
+      if (win[j]) L.ord[to] = static_cast<uint16_t>(nb[j]);
+      to += win[j] ? 1u : 0u;
+    }
   }
   lds_fence();
   return total;
@@ -335,11 +353,13 @@ __device__ EPass ell_search(const ELds& L, int32_t n, int32_t o, uint32_t root, 
     const int32_t width = fe - fb;
     int32_t next;
     if (width <= 16)
-      next = ell_near_level<W / 4, 4, false, kCheck>(L, fb, fe, passw, lowest);
+      next = ell_near_level<W / 4, 4, 1, false, kCheck>(L, fb, fe, passw, lowest);
     else if (width <= 32)
-      next = ell_near_level<W / 2, 2, false, kCheck>(L, fb, fe, passw, lowest);
+      next = ell_near_level<W / 2, 2, 1, false, kCheck>(L, fb, fe, passw, lowest);
     else if (width <= 64)
-      next = ell_near_level<W, 1, false, kCheck>(L, fb, fe, passw, lowest);
+      next = ell_near_level<W, 1, 1, false, kCheck>(L, fb, fe, passw, lowest);
+    else if (W == 4 && width <= 128)
+      next = ell_near_level<4, 1, 2, false, kCheck>(L, fb, fe, passw, lowest);
     else
       next = ell_search_level<W, 1, kCheck>(L, n, fb, fe, lvl, badm);
     next = uniform(next);
@@ -453,11 +473,13 @@ __device__ EPass ell_label(const ELds& L, int32_t n, int32_t o, uint32_t root, b
     int32_t placed;
     uint32_t unused = 0;
     if (width <= 16)
-      placed = ell_near_level<W / 4, 4, true, false>(L, b, e, 0u, unused);
+      placed = ell_near_level<W / 4, 4, 1, true, false>(L, b, e, 0u, unused);
     else if (width <= 32)
-      placed = ell_near_level<W / 2, 2, true, false>(L, b, e, 0u, unused);
+      placed = ell_near_level<W / 2, 2, 1, true, false>(L, b, e, 0u, unused);
     else if (width <= 64)
-      placed = ell_near_level<W, 1, true, false>(L, b, e, 0u, unused);
+      placed = ell_near_level<W, 1, 1, true, false>(L, b, e, 0u, unused);
+    else if (W == 4 && width <= 128)
+      placed = ell_near_level<4, 1, 2, true, false>(L, b, e, 0u, unused);
     else
       placed = ell_label_level<W, 1>(L, n, b, e);
     placed = uniform(placed);
@@ -684,7 +706,9 @@ __global__ void __launch_bounds__(kEThreads)
   bool longrow = false;
   long long bw = 0, prof = 0;
   int maxdeg = 0;
-  constexpr int kB = 8;
+  // (8 rows at a time take 2 us longer for a graph of up to 1,000 vertices,
+  // the fetching of the longer code, and nothing less for 4,000)
+  constexpr int kB = 2;
   for (int32_t v0 = tid; v0 < n; v0 += kEThreads * kB) {
     int32_t a[kB], b[kB];
     bool take[kB];

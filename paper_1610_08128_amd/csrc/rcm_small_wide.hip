@@ -35,7 +35,7 @@ constexpr int kWT = 1024;
 constexpr int kWWaves = kWT / 64;
 constexpr uint32_t kFree = 0xFFFFFFFFu;   // claim word: unclaimed, unstamped
 constexpr uint32_t kStamp = 0x80000000u;  // words from here on: not labelled
-constexpr int32_t kMaxN = 6144;
+constexpr int32_t kMaxN = 8192;
 constexpr int kPer = kMaxN / kWT;         // vertices per thread
 // Lanes of a row in a pass: 4 lanes of 4 entries took 1.12 times as long for a
 // graph of mean row 12, 8 lanes of 2 1.06 times (one wave's share of a level
@@ -47,7 +47,7 @@ constexpr int kBeginBits = 17;
 constexpr uint32_t kBeginMask = (1u << kBeginBits) - 1u;
 constexpr uint32_t kLenMask = (1u << 13) - 1u;
 constexpr int kDiagBit = 31;
-static_assert(kMaxN <= static_cast<int32_t>(kLenMask), "a row's length fits its field");
+static_assert(kMaxN <= static_cast<int32_t>(kLenMask) + 1, "a row's length fits its field");
 
 inline __host__ __device__ size_t al8(size_t x) { return (x + 7) & ~static_cast<size_t>(7); }
 
@@ -64,7 +64,7 @@ struct WLds {
   uint16_t* ord;   // order of the component (search queue, labels)
   uint16_t* orig;  // caller's id by number
   uint16_t* lst;   // a labelled level's children as they were found
-  uint32_t* todo;  // bitmap by caller's id: not ordered yet
+  uint32_t* todo;  // bitmap by caller's id: not ordered yet, isolated ones aside
 };
 
 struct WShared {
@@ -532,8 +532,18 @@ __global__ void __launch_bounds__(kWT) k_small_wide(SmallJob J, SmallOpts O) {
   extern __shared__ __align__(16) char smem[];
   __shared__ WShared S;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int32_t n = J.n, nnz = J.nnz;
+  const int32_t n = J.n;
+  const int32_t nnz = J.nnz >= 0 ? J.nnz : J.rowptr[n];
   SmallResult* R = J.res;
+  if (tid == 0) R->nnz = nnz;
+  if (nnz < 0) {
+    if (tid == 0) R->status = RCM_ERR_BAD_CSR;
+    return;
+  }
+  if (nnz >= 1 << kBeginBits || wide_bytes(n, nnz) > static_cast<size_t>(O.lds_bytes)) {
+    if (tid == 0) R->status = kSmallDeclined;
+    return;
+  }
   long long tk[7];
   tk[0] = wall_clock64();
   WLds L;
@@ -621,10 +631,7 @@ __global__ void __launch_bounds__(kWT) k_small_wide(SmallJob J, SmallOpts O) {
   // (the waves' bitmaps of the duplicate check, in ord and orig)
   const int32_t words = (n + 31) / 32;
   for (int32_t i = tid; i < kWWaves * words; i += kWT) reinterpret_cast<uint32_t*>(L.ord)[i] = 0;
-  for (int32_t i = tid; i < words; i += kWT) {
-    const int32_t left = n - 32 * i;
-    L.todo[i] = left >= 32 ? ~0u : (1u << left) - 1u;
-  }
+  for (int32_t i = tid; i < words; i += kWT) L.todo[i] = 0;
   __syncthreads();
   // rowptr must not decrease (checked once every entry is in LDS)
   for (int32_t i = tid; i + 1 < n; i += kWT) bad |= L.clm[i + 1] < L.clm[i];
@@ -648,6 +655,7 @@ __global__ void __launch_bounds__(kWT) k_small_wide(SmallJob J, SmallOpts O) {
     const int32_t d = deg[i];
     maxdeg = d > maxdeg ? d : maxdeg;
     isolated += d == 0 ? 1 : 0;
+    if (d > 0) atomicOr(&L.todo[i >> 5], 1u << (i & 31));
   }
   maxdeg = block_max(maxdeg, S.red[2]);
   isolated = block_sum(isolated, S.red[3]);
@@ -741,9 +749,9 @@ __global__ void __launch_bounds__(kWT) k_small_wide(SmallJob J, SmallOpts O) {
       err = RCM_ERR_ABORTED;
       break;
     }
-    // the lowest id not ordered yet (every wave finds it)
-    int32_t s = -1;
-    while (s < 0 && w_from < words) {
+    // the lowest id not ordered yet, isolated ones aside (every wave finds it)
+    int32_t s = n;
+    while (s == n && w_from < words) {
       const uint32_t word = w_from + lane < words ? L.todo[w_from + lane] : 0u;
       const unsigned long long m = __ballot(word != 0);
       if (m == 0) {
@@ -755,17 +763,39 @@ __global__ void __launch_bounds__(kWT) k_small_wide(SmallJob J, SmallOpts O) {
       s = 32 * w_from + __builtin_ctz(static_cast<uint32_t>(
                             __builtin_amdgcn_readlane(static_cast<int>(word), l)));
     }
-    if (s < 0) {  // fewer vertices reached than expected: cannot happen
+    // The isolated vertices have the lowest numbers, in the order of their
+    // ids: those before s are components of their own, in one go (two level
+    // structures and one level each).
+    int32_t next = alone;
+    for (int32_t hi = isolated; next < hi;) {
+      const int32_t mid = (next + hi) >> 1;
+      if (uniform(L.orig[mid]) < s) next = mid + 1;
+      else hi = mid;
+    }
+    if (next > alone) {
+      const int32_t run = next - alone;
+      for (int32_t t = tid; t < run; t += kWT) {
+        const int32_t id = L.orig[alone + t];
+        const int32_t at = O.reverse_mode ? n - 1 - o - t : o + t;
+        J.perm[at] = id + J.id_off;
+        if (J.iperm) J.iperm[id] = at + J.pos_off;
+        L.clm[alone + t] = static_cast<uint32_t>(o + t);
+      }
+      alone = next;
+      ncomp += run;
+      nbfs_all += 2 * run;
+      nlevels += run;
+      o += run;
+      since_poll += 64u * static_cast<uint32_t>(run - 1);
+      __syncthreads();
+      if (o >= n) break;
+    }
+    if (s == n) {  // fewer vertices reached than expected: cannot happen
       err = RCM_ERR_NOT_SYMMETRIC;
       break;
     }
     int32_t size = 1, nbfs = 2, levels = 1;
-    // the isolated vertices have the lowest numbers, in the order of their ids
-    if (alone < isolated && L.orig[alone] == s) {
-      if (tid == 0) L.ord[o] = static_cast<uint16_t>(alone);
-      ++alone;
-      __syncthreads();
-    } else {
+    {
       const long long ts0 = wall_clock64();
       for (int32_t r = tid; r < n; r += kWT)
         if (L.orig[r] == s) S.root = r;
@@ -902,29 +932,31 @@ __global__ void __launch_bounds__(kWT) k_small_wide(SmallJob J, SmallOpts O) {
     R->ticks[3] = t_label;
     R->ticks[4] = t_rev;
     R->ticks[5] = wall_clock64() - tk[3];
-    R->nnz = nnz;
     R->status = RCM_OK;
   }
 }
 
 }  // namespace
 
-// n from 64 (the waves' bitmaps of the duplicate check share 4 n bytes).
+// n from 64 (the waves' bitmaps of the duplicate check share 4 n bytes) to
+// below kMaxN (a row of every vertex still fits its length's field).
 size_t small_wide_lds_bytes(int64_t n, int64_t nnz) {
-  if (n < 64 || n > kMaxN || nnz >= 1 << kBeginBits) return ~static_cast<size_t>(0);
+  if (n < 64 || n >= kMaxN || nnz >= 1 << kBeginBits) return ~static_cast<size_t>(0);
   return wide_bytes(n, nnz) + kWideStatic;
 }
 
 hipError_t launch_small_wide(const SmallJob& job, const SmallOpts& opts, hipStream_t s) {
-  if (job.nnz < 0 ||
-      small_wide_lds_bytes(job.n, job.nnz) > static_cast<size_t>(opts.lds_bytes))
+  if (small_wide_lds_bytes(job.n, job.nnz < 0 ? 0 : job.nnz) >
+      static_cast<size_t>(opts.lds_bytes))
     return hipErrorInvalidValue;
-  const size_t need = wide_bytes(job.n, job.nnz);
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_small_wide),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           static_cast<int>(need));
+  SmallOpts o = opts;
+  o.lds_bytes = job.nnz < 0 ? opts.lds_bytes - static_cast<int32_t>(kWideStatic)
+                            : static_cast<int32_t>(wide_bytes(job.n, job.nnz));
+  const hipError_t e =
+      hipFuncSetAttribute(reinterpret_cast<const void*>(k_small_wide),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, o.lds_bytes);
   if (e != hipSuccess) return e;
-  k_small_wide<<<1, kWT, need, s>>>(job, opts);
+  k_small_wide<<<1, kWT, static_cast<size_t>(o.lds_bytes), s>>>(job, o);
   return hipGetLastError();
 }
 

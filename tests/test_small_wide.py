@@ -127,3 +127,27 @@ def test_refused_inputs(length):
     assert status(out) == rcm.ERR_BAD_CSR
     if length < n:
         assert status(rows, check_full=True) == rcm.ERR_NOT_SYMMETRIC
+
+
+@pytest.mark.parametrize("case", range(6))
+def test_more_vertices_than_the_records_fit(case):
+    """Short rows, up to the most vertices the engine takes; runs of isolated
+    vertices before, between and after the others."""
+    rng = np.random.default_rng(case)
+    if case == 0:
+        g = I.grid2d(79, 81, seed=1)
+    elif case == 1:
+        g = I.strip_drop(5, 1300, 0.02, seed=2)
+    elif case == 2:
+        g = I.random_tree(7900, 3)
+    elif case == 3:
+        # (a few long rows among 8,191 vertices, most of them isolated)
+        u, v = rng.integers(3000, 5000, 6000), rng.integers(3000, 5000, 6000)
+        g = I.from_edges(8191, u[u != v], v[u != v], diag=False, name="isolated_8191")
+    elif case == 4:
+        g = I.from_edges(8191, np.zeros(0, np.int64), np.zeros(0, np.int64), name="none_8191")
+    else:
+        u = rng.integers(0, 8190, 3000)
+        g = I.from_edges(8191, u, u + 1, diag=False, name="pairs_8191")
+    _check(g)
+    _check(g, reverse_mode=1, pp_variant=1)
