@@ -2295,10 +2295,10 @@ __device__ __forceinline__ void global_label_level(const BfsParams& P, Team& t, 
 //
 // (Graphs with a fixed-stride row copy only: no row is longer than a batch.)
 //
-// Leaves when a list grows too long, the level is narrow or the keys run out: the level's claims are then made again by
-// label, after the words of the vertices that could be mistaken for
-// unlabelled ones (this level's and the one's before) are set below every
-// label.
+// Leaves when a list grows too long, the level is narrow or the keys run out:
+// the level's claims are then made again by label, after the words of the
+// vertices that could be mistaken for unlabelled ones (this level's and the
+// one's before) are set below every label.
 //
 // What is left of a level is memory round trips across the dies: the words
 // read again and the ranks 2.0 us, the claims 2.5, the exchange 2.2.  Measured

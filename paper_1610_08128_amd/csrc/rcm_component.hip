@@ -179,6 +179,19 @@ __device__ __forceinline__ bool poll_abort(const ComponentParams& P, Lds& S, Ctx
 
 __device__ __forceinline__ uint32_t bit_of(uint32_t x) { return 1u << (x & 31u); }
 
+// x added to *p by one lane (the compiler would wrap a plain atomic of one
+// lane in a second reduction over the wave, 2 % of the 223 x 227 grid's time).
+__device__ __forceinline__ int32_t lds_add(int32_t* p, int32_t x) {
+  const uint32_t at = static_cast<uint32_t>(
+      reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) int32_t*)p));
+  int32_t old;
+  asm volatile("ds_add_rtn_u32 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(old)
+               : "v"(at), "v"(x)
+               : "memory");
+  return old;
+}
+
 // Which of the wave's active lanes' kN entries are new in a search: their
 // bits are set here, and *base is the first of the places reserved for them
 // in the next level (one atomic for the wave); at[j] is entry j's.
@@ -199,7 +212,7 @@ __device__ __forceinline__ void reserve(int32_t* cnt, const bool* fresh, int32_t
   if (total != 0) {
     const unsigned long long act = __ballot(true);
     if ((threadIdx.x & 63) == static_cast<unsigned>(__ffsll(static_cast<long long>(act)) - 1))
-      base = atomicAdd(cnt, total);
+      base = lds_add(cnt, total);
     base = __builtin_amdgcn_readfirstlane(base);
   }
 #pragma unroll
@@ -1043,19 +1056,6 @@ struct LongLds {
 };
 static_assert(sizeof(LongLds) <= 160 * 1024, "one work-group's LDS");
 
-// x added to *p by one lane (the compiler would wrap a plain atomic of one
-// lane in a second reduction over the wave).
-__device__ __forceinline__ int32_t lds_add(int32_t* p, int32_t x) {
-  const uint32_t at = static_cast<uint32_t>(
-      reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) int32_t*)p));
-  int32_t old;
-  asm volatile("ds_add_rtn_u32 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)"
-               : "=&v"(old)
-               : "v"(at), "v"(x)
-               : "memory");
-  return old;
-}
-
 // kN entries a lane of the rows of the level's vertices: the new ones, with
 // their rows, to the next level.  (A row's own vertex and its fillers are
 // marked already.)
@@ -1074,7 +1074,8 @@ __device__ __forceinline__ void long_reach(const ComponentParams& P, LongLds& S,
   for (int j = 0; j < kN; ++j) w[j] = mine[j];
 #pragma unroll
   for (int j = 0; j < kN; ++j)
-    old[j] = atomicOr(&S.bits[static_cast<uint32_t>(w[j]) >> 5], bit_of(static_cast<uint32_t>(w[j])));
+    old[j] = atomicOr(&S.bits[static_cast<uint32_t>(w[j]) >> 5],
+                      bit_of(static_cast<uint32_t>(w[j])));
 #pragma unroll
   for (int j = 0; j < kN; ++j) {
     fresh[j] = (old[j] & bit_of(static_cast<uint32_t>(w[j]))) == 0;

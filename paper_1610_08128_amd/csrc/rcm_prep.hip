@@ -139,6 +139,169 @@ __global__ void k_validate_scan(int32_t n, int32_t nnz, const int32_t* __restric
   if (wide) atomicOr(wide_rows, 1);
 }
 
+// The same for graphs whose rows hold more than 8 entries on average: 16 lanes
+// (a DPP row) take a row's entries side by side, two entries each in
+// registers, so that the rows of a wave are read as the few lines they are
+// and a long row is not one lane's work.  Ascending rows, which most are,
+// repeat nothing; in the others the entries in registers are compared pairwise
+// by rotating one side through the lanes.
+//
+// What bounds it are the round trips of the row pointers and the columns, so
+// a group has kBatch rows on their way at once.  Measured on MI355X, a row a
+// lane first: a random geometric graph of 100,003 vertices, mean row 13, 65
+// -> 17 us; a batch of 96 graphs of 2.6 million vertices together, 322 -> 243
+// us.  With shorter rows a row a lane is the faster form (the 128^3 grid: 47
+// us, 59 with eight lanes a row).
+constexpr uint32_t kNoColumn = 0x80000000u;  // above every column
+
+template <int kCtrl>
+__device__ __forceinline__ uint32_t dpp(uint32_t x) {
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
+      static_cast<int>(x), static_cast<int>(x), kCtrl, 0xf, 0xf, false));
+}
+// Equal pairs within a row's first or second 16 entries, and between them:
+// one side rotated by every step.
+template <int kStep>
+__device__ __forceinline__ uint32_t same_in(uint32_t x) {
+  if constexpr (kStep > 8) return 0u;
+  else return (x == dpp<0x120 + kStep>(x) ? 1u : 0u) | same_in<kStep + 1>(x);
+}
+template <int kStep>
+__device__ __forceinline__ uint32_t same_between(uint32_t x, uint32_t y) {
+  if constexpr (kStep > 15) return 0u;
+  else return (x == dpp<0x120 + kStep>(y) ? 1u : 0u) | same_between<kStep + 1>(x, y);
+}
+// The least value of the 16 lanes, in all of them.
+__device__ __forceinline__ uint32_t group_min(uint32_t x) {
+  uint32_t y = dpp<0xB1>(x);  // quad_perm: lane ^ 1
+  x = y < x ? y : x;
+  y = dpp<0x4E>(x);           // quad_perm: lane ^ 2
+  x = y < x ? y : x;
+  y = dpp<0x141>(x);          // row_half_mirror
+  x = y < x ? y : x;
+  y = dpp<0x140>(x);          // row_mirror
+  return y < x ? y : x;
+}
+
+__global__ void __launch_bounds__(kThreads)
+k_validate_long(int32_t n, int32_t nnz, const int32_t* __restrict__ rowptr,
+                const int32_t* __restrict__ colidx, int4* __restrict__ vinfo,
+                int32_t* __restrict__ beta, int32_t* __restrict__ err,
+                int32_t* __restrict__ long_rows, int4* __restrict__ ell,
+                int32_t* __restrict__ wide_rows) {
+  constexpr int kLanes = 16, kRows = kThreads / kLanes;
+  constexpr int kBatch = 4;
+  const int lane = threadIdx.x & 63;
+  const int32_t sub = static_cast<int32_t>(threadIdx.x) % kLanes;
+  const unsigned long long group = ((1ull << kLanes) - 1) << (lane & ~(kLanes - 1));
+  bool bad = false, wide = false, unsorted_long = false;
+  // kBatch rows a group at a time, whose loads are all on their way before the
+  // first is waited for (places past a row load its last entry again)
+  for (int64_t i0 = static_cast<int64_t>(blockIdx.x) * kRows * kBatch; i0 < n;
+       i0 += static_cast<int64_t>(gridDim.x) * kRows * kBatch) {
+    const int32_t first = static_cast<int32_t>(i0) + static_cast<int32_t>(threadIdx.x) / kLanes;
+    int32_t begin[kBatch], end[kBatch];
+    uint32_t e0[kBatch], e1[kBatch];
+#pragma unroll
+    for (int q = 0; q < kBatch; ++q) {
+      const int64_t r = static_cast<int64_t>(first) + q * kRows;
+      begin[q] = rowptr[r < n ? r : n];
+      end[q] = rowptr[r < n ? r + 1 : n];
+    }
+#pragma unroll
+    for (int q = 0; q < kBatch; ++q) {
+      const bool sound = begin[q] >= 0 && end[q] > begin[q] && end[q] <= nnz;
+      const int32_t k0 = begin[q] + sub, k1 = k0 + kLanes, top = end[q] - 1;
+      e0[q] = nnz > 0 ? static_cast<uint32_t>(colidx[sound ? (k0 < top ? k0 : top) : 0]) : 0u;
+      e1[q] = nnz > 0 ? static_cast<uint32_t>(colidx[sound ? (k1 < top ? k1 : top) : 0]) : 0u;
+    }
+#pragma unroll
+    for (int q = 0; q < kBatch; ++q) {
+      const int64_t row = static_cast<int64_t>(first) + q * kRows;
+      const bool act = row < n;
+      const int32_t i = static_cast<int32_t>(row);
+      const int32_t a = begin[q], b = end[q];
+      const bool broken = act && (a < 0 || b < a || b > nnz);
+      const int32_t len = act && !broken ? b - a : 0;
+      const uint32_t me = static_cast<uint32_t>(i);
+      const bool v0 = sub < len, v1 = sub + kLanes < len;
+      const uint32_t x0 = v0 ? e0[q] : kNoColumn | static_cast<uint32_t>(sub);
+      const uint32_t x1 = v1 ? e1[q] : kNoColumn | static_cast<uint32_t>(sub + kLanes);
+      const bool second = __any(len > kLanes);
+      bad |= broken || (v0 && x0 >= static_cast<uint32_t>(n)) ||
+             (v1 && x1 >= static_cast<uint32_t>(n));
+      bool self = x0 == me;
+      uint32_t mn = x0 < me ? x0 : me;
+      bool up = sub == 0 || dpp<0x111>(x0) < x0;
+      if (second) {
+        self |= x1 == me;
+        mn = x1 < mn ? x1 : mn;
+        const uint32_t before = dpp<0x111>(x1), last = dpp<0x140>(x0);
+        up &= (sub == 0 ? last : before) < x1;
+      }
+      if (__any(len > 2 * kLanes)) {
+        uint32_t prev = x1;
+        for (int32_t k = sub + 2 * kLanes; __any(k - sub < len); k += kLanes) {
+          uint32_t x = kNoColumn | static_cast<uint32_t>(k);
+          if (k < len) {
+            x = static_cast<uint32_t>(colidx[a + k]);
+            bad |= x >= static_cast<uint32_t>(n);
+          }
+          self |= x == me;
+          mn = x < mn ? x : mn;
+          const uint32_t before = dpp<0x111>(x), last = dpp<0x140>(prev);
+          up &= (sub == 0 ? last : before) < x;
+          prev = x;
+        }
+      }
+      const unsigned long long down = __ballot(!up);
+      if (down != 0) {
+        uint32_t same = same_in<1>(x0);
+        if (second)
+          same |= same_in<1>(x1) | (x0 == x1 ? 1u : 0u) |
+                  same_between<1>(x0, x1);
+        bad |= same != 0;
+        if (len > 2 * kLanes && (down & group) != 0) {
+          if (len <= kDupShort) {
+            // (each entry is met once)
+            for (int32_t k = sub; k < len; k += kLanes) {
+              const int32_t c = colidx[a + k];
+              int met = 0;
+              for (int32_t k2 = a; k2 < b; ++k2) met += colidx[k2] == c ? 1 : 0;
+              bad |= met != 1;
+            }
+          } else {
+            unsorted_long = true;
+          }
+        }
+      }
+      const bool diag = (__ballot(self) & group) != 0;
+      mn = group_min(mn);
+      if (sub == 0 && act) {
+        vinfo[i] = broken ? make_int4(0, 0, 0, i) : make_int4(a, b, len - (diag ? 1 : 0), i);
+        beta[i] = broken ? 0 : i - static_cast<int32_t>(mn);
+      }
+      if (ell != nullptr && act && !broken) {
+        // the row, then the vertex itself in the unused places
+        static_assert(kEllWidth <= kLanes, "a lane an entry");
+        const bool copied = len <= kEllWidth;
+        wide |= !copied;
+        if (sub < kEllWidth)
+          reinterpret_cast<int32_t*>(ell + 2 * static_cast<size_t>(i))[sub] =
+              copied ? (v0 ? static_cast<int32_t>(x0) : i) : -1;
+      }
+    }
+  }
+  // (one lane of a wave, and only until the word is raised: most rows of a
+  // graph can be wide, and 25,000 waves' atomics on one word take 0.2 ms)
+  auto raise = [&](bool mine, int32_t* word) {
+    if (__any(mine) && lane == 0 && ld_relaxed(word) == 0) atomicOr(word, 1);
+  };
+  raise(bad, err);
+  raise(wide, wide_rows);
+  raise(unsorted_long, long_rows);
+}
+
 // Duplicates in the rows longer than kDupShort: one work-group per row,
 // which inserts the row's columns into a hash set in LDS (open addressing,
 // atomic compare-and-swap); finding a column already there is a repeat.  A
@@ -222,32 +385,49 @@ k_dup_long(int32_t n, int32_t nnz, const int32_t* __restrict__ rowptr,
 // Every column of a graph's rows lies inside that graph.  Blocks take tiles
 // of kSegTile consecutive rows, find the graph of a tile's first row once and
 // step forward over the graph boundaries inside it.
-constexpr int kSegPer = 8;
-constexpr int32_t kSegTile = kThreads * kSegPer;
+// Eight lanes share a row, and a lane's rows of a tile are loaded together (a
+// row a lane, entry after entry: 94 us for a batch of 2.6 million vertices,
+// 73 so).
+constexpr int32_t kSegTile = kThreads;
+constexpr int kRowLanes = 8;
+constexpr int kRowGroups = kThreads / kRowLanes;
 
-__global__ void k_check_segments(int32_t n, int32_t nnz, const int32_t* __restrict__ rowptr,
-                                 const int32_t* __restrict__ colidx,
-                                 const int32_t* __restrict__ seg_off, int nseg,
-                                 int32_t* __restrict__ err) {
+__global__ void __launch_bounds__(kThreads)
+k_check_segments(int32_t n, int32_t nnz, const int32_t* __restrict__ rowptr,
+                 const int32_t* __restrict__ colidx, const int32_t* __restrict__ seg_off,
+                 int nseg, int32_t* __restrict__ err) {
   const int64_t tiles = (static_cast<int64_t>(n) + kSegTile - 1) / kSegTile;
+  const int32_t sub = static_cast<int32_t>(threadIdx.x) % kRowLanes;
+  bool bad = false;
   for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
     const int64_t base = t * kSegTile;
     int s = find_segment(seg_off, nseg, static_cast<int32_t>(base));
-    for (int j = 0; j < kSegPer; ++j) {
-      const int64_t x = base + static_cast<int64_t>(j) * kThreads + threadIdx.x;
-      if (x >= n) break;
-      const int32_t i = static_cast<int32_t>(x);
+    constexpr int kRows = kSegTile / kRowGroups;
+    const int64_t first = base + threadIdx.x / kRowLanes;
+    int32_t a[kRows], b[kRows], c[kRows];
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) {
+      const int64_t x = first + j * kRowGroups;
+      a[j] = rowptr[x < n ? x : n];
+      b[j] = rowptr[x < n ? x + 1 : n];
+      if (a[j] < 0 || b[j] <= a[j] || b[j] > nnz) a[j] = b[j] = 0;  // (or empty)
+    }
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) {
+      const int32_t k = a[j] + sub;
+      c[j] = nnz > 0 ? colidx[k < b[j] ? k : a[j]] : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) {
+      const int32_t i = static_cast<int32_t>(first) + j * kRowGroups;
       while (s + 1 < nseg && i >= seg_off[s + 1]) ++s;
       const int32_t lo = seg_off[s], hi = seg_off[s + 1];
-      const int32_t a = rowptr[i];
-      const int32_t b = rowptr[i + 1];
-      if (a < 0 || b < a || b > nnz) continue;
-      for (int32_t k = a; k < b; ++k) {
-        const int32_t c = colidx[k];
-        if (c < lo || c >= hi) { atomicOr(err, 1); break; }
-      }
+      bad |= b[j] > a[j] && (c[j] < lo || c[j] >= hi);
+      for (int32_t k = a[j] + sub + kRowLanes; k < b[j]; k += kRowLanes)
+        bad |= colidx[k] < lo || colidx[k] >= hi;
     }
   }
+  if (bad) atomicOr(err, 1);
 }
 
 // Vertices and threads per block of k_seg_reduce, whose blocks end in two
@@ -880,8 +1060,12 @@ hipError_t launch_exclusive_scan(const int32_t* in, int32_t* out, int32_t count,
 hipError_t launch_validate_scan(const Graph& g, int4* vinfo, int32_t* beta, SegStats* seg,
                                 int32_t* err, int32_t* long_rows, int4* ell,
                                 int32_t* wide_rows, hipStream_t s) {
-  k_validate_scan<<<grid_for(g.n, kThreads), kThreads, 0, s>>>(
-      g.n, g.nnz, g.rowptr, g.colidx, vinfo, beta, err, long_rows, ell, wide_rows);
+  if (static_cast<int64_t>(g.nnz) > 8 * static_cast<int64_t>(g.n))
+    k_validate_long<<<grid_for(4 * static_cast<int64_t>(g.n), kThreads), kThreads, 0, s>>>(
+        g.n, g.nnz, g.rowptr, g.colidx, vinfo, beta, err, long_rows, ell, wide_rows);
+  else
+    k_validate_scan<<<grid_for(g.n, kThreads), kThreads, 0, s>>>(
+        g.n, g.nnz, g.rowptr, g.colidx, vinfo, beta, err, long_rows, ell, wide_rows);
   if (g.nseg > 1)
     k_check_segments<<<grid_for((static_cast<int64_t>(g.n) + kSegTile - 1) / kSegTile, 1),
                        kThreads, 0, s>>>(g.n, g.nnz, g.rowptr, g.colidx, g.seg_off, g.nseg, err);

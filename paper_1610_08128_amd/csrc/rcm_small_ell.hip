@@ -26,9 +26,9 @@
 //   scalar: both are a third of the instructions, which is what a level's
 //   time was (the 64 x 64 grid: 0.45 us a search level and 0.40 a labelled
 //   one before, 0.27 and 0.28 now; the call 216 -> 154 us, the 32 x 32
-//   grid's 93 -> 75).  Forms for 256 vertices, or for 128 with rows of 8,
-//   took every level twice as long: the kernel then needs 248 registers and
-//   87 KB of code.
+//   grid's 93 -> 75).  With forms for 256 vertices, and for 128 with rows of
+//   8, every level took twice as long: the kernel then needs 248 registers,
+//   and its code grows by half.
 // - The bulk phases (loading with the checks, the row sort, the statistics
 //   of the result) run on eight waves; the level loops, whose levels are a
 //   wave wide on such graphs, run on the first wave alone while the others
