@@ -925,8 +925,11 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
     const size_t temp_need = level_order_temp_bytes(g.n);
     const size_t temp_have = L.scan_blk - L.t_single;
     if (temp_need == 0 || temp_need > temp_have) return RCM_ERR_WORKSPACE_TOO_SMALL;
+    // (no degree reaches the entry count or the vertex count, or passes the
+    // copy's width where every row fits that)
+    const int64_t top = ell != nullptr ? kEllWidth : std::min<int64_t>(g.nnz, g.n);
     int32_t deg_bits = 1;
-    while (deg_bits < 31 && (1ll << deg_bits) <= g.nnz) ++deg_bits;
+    while (deg_bits < 31 && (1ll << deg_bits) <= top) ++deg_bits;
     HIP_TRY(launch_level_order(g.n, deg_bits, opt.label_mode == 2, vinfo,
                                reinterpret_cast<const int32_t*>(claim), perm_out, iperm,
                                ws + L.qi, ws + L.t_single, temp_have, s));

@@ -44,16 +44,20 @@ inline unsigned bits_for(int64_t n) {
   return b;
 }
 
-// vals[i] = n - 1 - i (descending id) and its first sort key: the degree
-// complement (ordering by degree) or the position key.
-__global__ void k_lo_init(int32_t n, int32_t by_degree, uint32_t deg_max,
+// vals[i] = n - 1 - i (descending id) and its first sort key: the position
+// key, the degree complement, or the one above the other's deg_bits bits.
+enum { kByKey = 0, kByDegree, kByBoth };
+__global__ void k_lo_init(int32_t n, int32_t by, uint32_t deg_max, unsigned deg_bits,
                           const int4* __restrict__ vinfo, const int32_t* __restrict__ key,
                           uint32_t* __restrict__ key_out, int32_t* __restrict__ val_out) {
   for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     const int32_t v = n - 1 - i;
     val_out[i] = v;
-    key_out[i] = by_degree ? deg_max - static_cast<uint32_t>(vinfo[v].z)
-                           : static_cast<uint32_t>(key[v]);
+    uint32_t k = 0;
+    if (by != kByDegree) k = static_cast<uint32_t>(key[v]);
+    if (by == kByBoth) k <<= deg_bits;
+    if (by != kByKey) k |= deg_max - static_cast<uint32_t>(vinfo[v].z);
+    key_out[i] = k;
   }
 }
 
@@ -224,10 +228,14 @@ hipError_t launch_level_order(int32_t n, int32_t max_degree_bits, bool by_degree
   const unsigned deg_bits = static_cast<unsigned>(max_degree_bits);
   const uint32_t deg_max = deg_bits >= 32 ? 0xFFFFFFFFu : ((1u << deg_bits) - 1u);
   const int g = grid_for(n);
-  k_lo_init<<<g, kThreads, 0, s>>>(n, by_degree ? 1 : 0, deg_max, vinfo, key, ka, va);
+  const bool both = by_degree && key_bits + deg_bits <= 32;
+  k_lo_init<<<g, kThreads, 0, s>>>(n, both ? kByBoth : (by_degree ? kByDegree : kByKey), deg_max,
+                                   deg_bits, vinfo, key, ka, va);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (by_degree) {
+  if (both) {
+    e = sort_pairs(temp, temp_bytes, ka, va, kb, vb, perm, n, key_bits + deg_bits, s);
+  } else if (by_degree) {
     // by degree into vb, then the keys gathered again in that order
     e = sort_pairs(temp, temp_bytes, ka, va, kb, vb, vb, n, deg_bits, s);
     if (e != hipSuccess) return e;
