@@ -125,7 +125,8 @@ typedef struct {
                             batched calls)                                     */
   int32_t narrow_cutoff; /* levels narrower than this are expanded by one
                             work-group of the team without grid-wide barriers;
-                            0 = auto (256), -1 = never                         */
+                            0 = auto (128 for a single graph whose rows hold at
+                            most 8 entries, else 256), -1 = never              */
   int32_t small_threads; /* threads per work-group of the single-work-group
                             teams; 0 = auto (256); 256 or 512                  */
   int32_t max_teams;     /* most large-component teams run at once; 0 = auto

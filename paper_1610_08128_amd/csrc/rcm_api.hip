@@ -42,7 +42,7 @@ struct Opts {
   int threads = 256;
   int small_threads = 256;
   int small_cutoff = 1 << 18;
-  int narrow_cutoff = 256;
+  int narrow_cutoff = 0;  // 0: by the rows, see narrow_for
   int max_teams = 16;
   // batched call with team_size and max_teams left to auto: a batch of many
   // large components, none of them very large, gets many small teams
@@ -103,6 +103,15 @@ inline bool window_enabled() {
 inline int team_for(const Opts& o, int64_t n) {
   if (o.team_size > 0) return o.team_size;
   return n >= (1 << 18) ? 256 : 64;
+}
+
+// Levels that a team leaves to one work-group.  One barrier a level costs the
+// team about what a narrow level costs that work-group where the rows have
+// their copy (2D grids of 150^2 / 300^2 / 900^2 with 256, 128 and 64: the
+// labelled BFS 1.41, 1.42, 1.53 / 3.85, 3.25, 3.30 / 11.0, 10.25, 10.28 ms;
+// 60 x 60 x 61 1.19, 1.11, 1.10); two barriers and longer rows cost more.
+inline int narrow_for(const Opts& o, bool copied) {
+  return o.narrow_cutoff != 0 ? o.narrow_cutoff : (copied ? 128 : 256);
 }
 
 // Whether any launch option of the team kernel is set.
@@ -534,7 +543,6 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
   P.nnz = g.nnz;
   P.pp_variant = opt.pp_variant;
   P.reverse_mode = opt.reverse_mode;
-  P.narrow_cutoff = opt.narrow_cutoff;
   P.rebalance = opt.rebalance;
   P.label_mode = opt.label_mode;
   P.async_search = opt.async_search;
@@ -548,6 +556,7 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
   P.relabelled = 0;
   P.new_of_old = nullptr;
   P.ell = g.nseg == 1 ? ell : nullptr;
+  P.narrow_cutoff = narrow_for(opt, P.ell != nullptr && opt.threads <= 256);
   // Before the first launch of the team kernel: no vertex visited or claimed,
   // and the distance words of the asynchronous passes below every pass tag.
   // (After a probe by the component engine that is behind the search for the
@@ -805,6 +814,7 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
         P.relabelled = 1;
         P.resume = 1;
         P.ell = nullptr;  // the copy holds the caller's numbering
+        P.narrow_cutoff = narrow_for(opt, false);
         st = launch(t_big, 1, nullptr, 0, 1, true, false);
         P = saved;
         if (st != RCM_OK) return st;
