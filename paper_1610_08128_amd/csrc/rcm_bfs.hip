@@ -131,7 +131,11 @@ constexpr uint32_t kOrderedKeys = 0x80000000u;
 // to kLongKids children in registers itself; one with many more on a long
 // row is placed by the whole work-group (kHeavyCap: such parents per chunk
 // of the level, at most one per thread).
-constexpr int kLongKids = 4;
+// (Random geometric graphs of 100,000 / 2,000,000 vertices, mean row 13, where
+// the smallest label of a level has up to a dozen children: a labelled level
+// 41 / 53 us with 4, 30 / 41 with 8, 24 / 28 with 12, 27 / 30 with 16, whose
+// selects cost more than the few rescanned rows.)
+constexpr int kLongKids = 12;
 constexpr int kHeavyCap = 512;
 // A parent's own ranking of c > kLongKids children scans its row once per
 // child: c * (row batches) dependent round trips.  Past this many, the
@@ -1579,7 +1583,7 @@ __device__ __forceinline__ void defer_claims(const BfsParams& P, Shared& S, int3
 
 // Children of parent p (vertex u, row [a, b)) ranked by (degree, id) among
 // the siblings, for rows longer than a register batch.  One pass over the row
-// collects the keys of up to four children in registers (placed by
+// collects the keys of up to kLongKids children in registers (placed by
 // predicated selects, no indexed register access); they are ranked there and
 // their records fetched together.  A parent with more children ranks each
 // one against the whole row (place_many_children takes the parents for which
