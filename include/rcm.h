@@ -111,7 +111,7 @@ typedef struct {
                             partner row's length)                              */
   int32_t team_size;     /* work-groups cooperating on one large component;
                             0 = auto (256, one per compute unit, for graphs
-                            of at least 2^18 vertices, else 64; 8 in batched
+                            of at least 2^15 vertices, else 64; 8 in batched
                             calls, 4 for a batch with more large components
                             than 8-wide teams start at once and no graph of
                             2^18 vertices or more); 1..256, capped at the

@@ -97,12 +97,14 @@ inline bool window_enabled() {
   return !(e && e[0] == '0');
 }
 
-// Auto team size of a single graph: all compute units for a large graph
-// (its asynchronous search passes speed up up to one work-group per CU),
-// 64 for a smaller one, whose narrow levels only pay for more barrier slots.
+// Auto team size of a single graph: all compute units, on which its
+// asynchronous search passes spread (the two of the 40^3 / 60 x 60 x 61 grids
+// on 64, 128 and 256 work-groups: 0.62, 0.59, 0.57 / 1.04, 0.91, 0.84 ms; of
+// the 400^2 grid 2.98, 2.57, 2.52), the labelled levels being label_team's; 64
+// for a graph so small that a level hardly fills those.
 inline int team_for(const Opts& o, int64_t n) {
   if (o.team_size > 0) return o.team_size;
-  return n >= (1 << 18) ? 256 : 64;
+  return n >= (1 << 15) ? 256 : 64;
 }
 
 // Levels that a team leaves to one work-group.  One barrier a level costs the
