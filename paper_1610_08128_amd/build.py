@@ -18,9 +18,11 @@ INCLUDE = os.path.join(ROOT, "include")
 OUT = os.path.join(PKG, "librcm.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
 
-SOURCES = ["rcm_prep.hip", "rcm_bfs.hip", "rcm_api.hip", "rcm_server.hip", "rcm_apply.hip",
+SOURCES = ["rcm_bfs.hip", "rcm_bfs_csr.hip", "rcm_bfs_wide.hip", "rcm_prep.hip", "rcm_api.hip",
+           "rcm_server.hip", "rcm_apply.hip",
            "rcm_levelorder.hip", "rcm_noalloc.hip", "rcm_small.hip", "rcm_small_ell.hip",
-           "rcm_small_wide.hip", "rcm_tuning.hip", "rcm_relabel.hip", "rcm_window.hip", "rcm_component.hip"]
+           "rcm_small_wide.hip", "rcm_tuning.hip", "rcm_relabel.hip", "rcm_window.hip",
+           "rcm_component.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

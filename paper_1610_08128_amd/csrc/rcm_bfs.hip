@@ -134,8 +134,13 @@ constexpr uint32_t kOrderedKeys = 0x80000000u;
 // (Random geometric graphs of 100,000 / 2,000,000 vertices, mean row 13, where
 // the smallest label of a level has up to a dozen children: a labelled level
 // 41 / 53 us with 4, 30 / 41 with 8, 24 / 28 with 12, 27 / 30 with 16, whose
-// selects cost more than the few rescanned rows.)
+// selects cost more than the few rescanned rows.)  Their records are fetched
+// kLongGroup at a time: all twelve at once took 26 registers more in the
+// instance without a row copy, and cost the 512-thread one 3 % on grids (568
+// more spilled, 80^3 3.92 -> 4.05 ms, 3.93 so).
 constexpr int kLongKids = 12;
+constexpr int kLongGroup = 4;
+static_assert(kLongKids % kLongGroup == 0, "whole groups");
 constexpr int kHeavyCap = 512;
 // A parent's own ranking of c > kLongKids children scans its row once per
 // child: c * (row batches) dependent round trips.  Past this many, the
@@ -1583,16 +1588,16 @@ __device__ __forceinline__ void defer_claims(const BfsParams& P, Shared& S, int3
 
 // Children of parent p (vertex u, row [a, b)) ranked by (degree, id) among
 // the siblings, for rows longer than a register batch.  One pass over the row
-// collects the keys of up to kLongKids children in registers (placed by
+// collects the keys of up to kKids children in registers (placed by
 // predicated selects, no indexed register access); they are ranked there and
 // their records fetched together.  A parent with more children ranks each
 // one against the whole row (place_many_children takes the parents for which
 // that would be long).
+template <int kKids>
 __device__ __forceinline__ void place_long_row(const BfsParams& P, Shared& S, int32_t p, int32_t u,
                                                int32_t a, int32_t b, int32_t base, int32_t end,
                                                int32_t list_base, long long& my_m) {
   const uint32_t pl = static_cast<uint32_t>(p);
-  constexpr int kKids = kLongKids;  // children ranked in registers
   uint64_t ck[kKids];  // their (degree, caller id) keys ...
   int32_t cv[kKids];   // ... and vertex numbers
 #pragma unroll
@@ -1623,20 +1628,24 @@ __device__ __forceinline__ void place_long_row(const BfsParams& P, Shared& S, in
     }
   }
   if (nc <= kKids) {
-    int4 inf[kKids];
 #pragma unroll
-    for (int i = 0; i < kKids; ++i) inf[i] = P.vinfo[cv[i]];
+    for (int g = 0; g < kKids; g += kLongGroup) {
+      int4 inf[kLongGroup];
 #pragma unroll
-    for (int i = 0; i < kKids; ++i) {
-      if (i >= nc) continue;
-      int rank = 0;
+      for (int i = 0; i < kLongGroup; ++i) inf[i] = P.vinfo[cv[g + i]];
+      asm volatile("" ::: "memory");  // keeps the next group's loads behind
 #pragma unroll
-      for (int x = 0; x < kKids; ++x) rank += ck[x] < ck[i] ? 1 : 0;
-      const int32_t v = cv[i];
-      const int32_t at = base + rank;
-      if (at < end) st_rec(&P.qi[at], record(v, inf[i]));
-      my_m += inf[i].z;
-      defer_claims(P, S, v, inf[i], at, list_base);
+      for (int i = 0; i < kLongGroup; ++i) {
+        if (g + i >= nc) continue;
+        int rank = 0;
+#pragma unroll
+        for (int x = 0; x < kKids; ++x) rank += ck[x] < ck[g + i] ? 1 : 0;
+        const int32_t v = cv[g + i];
+        const int32_t at = base + rank;
+        if (at < end) st_rec(&P.qi[at], record(v, inf[i]));
+        my_m += inf[i].z;
+        defer_claims(P, S, v, inf[i], at, list_base);
+      }
     }
     return;
   }
@@ -2217,7 +2226,11 @@ __device__ __forceinline__ void global_label_level(const BfsParams& P, Team& t, 
           const int h = atomicAdd(&S.nheavy, 1);
           S.heavy[h] = make_int4(p, base, c, 0);
         } else {
-          place_long_row(P, S, p, e.x, e.y, e.z, base, end, list_base, my_m);
+          // (with a row copy no row is that long: the smallest code there)
+          if (P.ell != nullptr)
+            place_long_row<kLongGroup>(P, S, p, e.x, e.y, e.z, base, end, list_base, my_m);
+          else
+            place_long_row<kLongKids>(P, S, p, e.x, e.y, e.z, base, end, list_base, my_m);
         }
       }
     }
@@ -2972,17 +2985,19 @@ __device__ __forceinline__ void order_main(const BfsParams& P) {
   }
 }
 
-// Two instances of the same kernel, one per work-group size.  Bounded at
-// 256 threads, a wave may use all 512 registers of a lane (256 vector and
-// 256 accumulator registers) and the kernel compiles without any scratch
-// spill; bounded at 512 it gets 256 and spills (about 170 vector registers
-// to scratch).  On the 128^3 grid both take the same time (the labelled
-// pass is faster without the spills, the asynchronous search slightly
-// slower), so 256-thread work-groups, the default, run the spill-free
-// instance, and 512-thread ones the other (on the CSR only).
-__global__ void __launch_bounds__(256) k_order(BfsParams P) {
-  order_main(P);
-}
+}  // namespace
+
+// Three instances of the same kernel, each compiled in a source of its own
+// (rcm_bfs_csr.hip and rcm_bfs_wide.hip include this one), since one takes two
+// minutes.  Bounded at 256 threads, a wave may use all 512 registers of a
+// lane (256 vector and 256 accumulator registers) and the kernel compiles
+// without any scratch spill; bounded at 512 it gets 256 and spills (410
+// vector registers to scratch).  256-thread work-groups, the default, take
+// one of the spill-free instances: with the fixed-stride row copy, or without.
+// Apart, they need 82 and 88 accumulator registers, 124 as one; the
+// asynchronous levels of a 35 x 10,000 strip under a level order took 47.0 ms
+// as one and 46.3 apart.
+#if defined(RCM_ORDER_WIDE)
 
 __global__ void __launch_bounds__(512) k_order_wide(BfsParams P) {
   // the fixed-stride row path holds a row per neighbour in registers, which
@@ -2992,9 +3007,34 @@ __global__ void __launch_bounds__(512) k_order_wide(BfsParams P) {
   order_main(Q);
 }
 
-const void* order_kernel(int32_t threads) {
-  return threads > 256 ? reinterpret_cast<const void*>(k_order_wide)
-                       : reinterpret_cast<const void*>(k_order);
+const void* order_kernel_wide() { return reinterpret_cast<const void*>(k_order_wide); }
+
+#elif defined(RCM_ORDER_CSR)
+
+__global__ void __launch_bounds__(256) k_order_csr(BfsParams P) {
+  BfsParams Q = P;
+  Q.ell = nullptr;
+  order_main(Q);
+}
+
+const void* order_kernel_csr() { return reinterpret_cast<const void*>(k_order_csr); }
+
+#else
+
+__global__ void __launch_bounds__(256) k_order(BfsParams P) {
+  BfsParams Q = P;
+  if (Q.ell == nullptr) __builtin_unreachable();  // launch_order picks by it
+  order_main(Q);
+}
+
+const void* order_kernel_csr();
+const void* order_kernel_wide();
+
+namespace {
+
+const void* order_kernel(int32_t threads, bool rows) {
+  if (threads > 256) return order_kernel_wide();
+  return rows ? reinterpret_cast<const void*>(k_order) : order_kernel_csr();
 }
 
 // Cooperative launches of this library in one process never overlap: each
@@ -3005,10 +3045,15 @@ std::mutex g_coop_mutex;
 }  // namespace
 
 int max_team_blocks(int32_t threads) {
+  // what fits whichever instance a launch takes
   int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, order_kernel(threads), threads, 0) !=
-      hipSuccess)
-    return 0;
+  for (const bool rows : {false, true}) {
+    int fit = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, order_kernel(threads, rows), threads,
+                                                     0) != hipSuccess)
+      return 0;
+    per_cu = rows && per_cu < fit ? per_cu : fit;
+  }
   int dev = 0;
   (void)hipGetDevice(&dev);
   int cus = 0;
@@ -3020,22 +3065,20 @@ hipError_t launch_order(const BfsParams& p, int32_t blocks, int32_t threads, hip
   if (blocks <= 0 || (p.n_big <= 0 && p.ntasks <= 0)) return hipSuccess;
   if (threads != 256 && threads != 512) return hipErrorInvalidValue;
   BfsParams q = p;
+  const void* kernel = order_kernel(threads, q.ell != nullptr);
+  void* args[] = {&q};
   if (q.big_blocks > 0 && q.team_size > 1) {
     // held until the kernel has finished, so that another thread's
     // cooperative launch (a second stream of the serving engine, say) cannot
     // take part of the device while this one's teams wait for each other
     std::lock_guard<std::mutex> lk(g_coop_mutex);
-    void* args[] = {&q};
-    hipError_t e = hipLaunchCooperativeKernel(order_kernel(threads), dim3(blocks), dim3(threads),
-                                              args, 0, s);
+    hipError_t e = hipLaunchCooperativeKernel(kernel, dim3(blocks), dim3(threads), args, 0, s);
     if (e != hipSuccess) return e;
     return hipStreamSynchronize(s);
   }
-  if (threads > 256)
-    k_order_wide<<<blocks, threads, 0, s>>>(q);
-  else
-    k_order<<<blocks, threads, 0, s>>>(q);
-  return hipGetLastError();
+  return hipLaunchKernel(kernel, dim3(blocks), dim3(threads), args, 0, s);
 }
+
+#endif
 
 }  // namespace rcm
