@@ -12,6 +12,8 @@
 
 #include "rcm_apply.h"
 
+#include <algorithm>
+
 #include <hip/hip_runtime.h>
 
 #include "rcm_common.hpp"
@@ -35,7 +37,10 @@ struct ApplyLayout {
   size_t deg, begin, blk, counts, sort, total;
 };
 
-ApplyLayout apply_layout(int32_t n, int64_t nnz) {
+// The workspace asked for has room for a copy of the columns and values as
+// well, although rows are sorted where they are read: the size is part of the
+// interface, so a workspace below it is refused as it always was.
+ApplyLayout apply_layout(int32_t n, int64_t nnz, bool with_values) {
   ApplyLayout L{};
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -49,7 +54,8 @@ ApplyLayout apply_layout(int32_t n, int64_t nnz) {
   L.blk = take(4 * (N / 4096 + 2));
   L.counts = take(8);     // medium and long rows
   L.sort = take(8 * M);  // (column, position) pairs of rows too long for LDS
-  L.total = off;
+  const size_t copies = align_up(4 * M) + (with_values ? align_up(8 * M) : 0);
+  L.total = std::max(off, off - align_up(4 * N) + copies);
   return L;
 }
 
@@ -387,9 +393,8 @@ using namespace rcm;
 extern "C" {
 
 size_t rcm_permute_workspace_bytes(int32_t n, int64_t nnz, int32_t with_values) {
-  (void)with_values;  // values are read where they are
   if (n <= 0 || nnz < 0 || nnz >= (1ll << 31) - 1) return 0;
-  return apply_layout(n, nnz).total;
+  return apply_layout(n, nnz, with_values != 0).total;
 }
 
 rcm_status rcm_permute(int32_t n, int64_t nnz, const int32_t* rowptr, const int32_t* colidx,
@@ -401,7 +406,7 @@ rcm_status rcm_permute(int32_t n, int64_t nnz, const int32_t* rowptr, const int3
   if (!rowptr || !perm || !iperm || !rowptr_out || (nnz > 0 && (!colidx || !colidx_out)))
     return RCM_ERR_INVALID_ARGUMENT;
   if (vals && !vals_out) return RCM_ERR_INVALID_ARGUMENT;
-  const ApplyLayout L = apply_layout(n, nnz);
+  const ApplyLayout L = apply_layout(n, nnz, vals != nullptr);
   if (!workspace || workspace_bytes < L.total) return RCM_ERR_WORKSPACE_TOO_SMALL;
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
