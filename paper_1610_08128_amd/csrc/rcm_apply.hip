@@ -55,7 +55,7 @@ ApplyLayout apply_layout(int32_t n, int64_t nnz, bool with_values) {
   L.counts = take(8);     // medium and long rows
   L.sort = take(8 * M);  // (column, position) pairs of rows too long for LDS
   const size_t copies = align_up(4 * M) + (with_values ? align_up(8 * M) : 0);
-  L.total = std::max(off, off - align_up(4 * N) + copies);
+  L.total = std::max(off, off - align_up(4 * N) - align_up(8) + copies);
   return L;
 }
 
