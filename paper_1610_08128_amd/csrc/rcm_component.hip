@@ -48,7 +48,11 @@ constexpr int kHeavyCap = 32;
 constexpr int kScanAll = 512;       // parents a single wave scans
 constexpr int32_t kNone = -1;
 constexpr uint32_t kSelf = 0x80000000u;  // the row holds its diagonal entry
-constexpr int32_t kLongRow = 1 << 24;    // added to a level's count: a row too long for the copy
+// A level's answer when a vertex of it has a row too long for the copy.  What
+// says so is a word of its own (Lds::cnt's second), never part of the count:
+// each of up to kThreads vertices can be found by another lane.
+constexpr int32_t kLongRow = 1 << 24;
+static_assert(kLongRow > kComponentRange, "no level holds as many vertices");
 
 // The next level's table of a labelled level: vertex and smallest parent's
 // index in the level, at most half full (see reach_label), the slot of each
@@ -90,7 +94,9 @@ struct Lds {
     EllLds ell;
   };
   int32_t wtot[kWaves];
-  int2 cnt[3];                // level mod 3: size of the level being found, long rows seen
+  int2 cnt[3];                // level mod 3: size of the level being found, and of its rows
+                              // the long ones (CsrLevels: so many are to be read by the
+                              // work-group; EllLevels: 1 = one is too long for the copy)
   int32_t heavy[kHeavyCap];
   unsigned long long key;
   long long red[16];
@@ -465,7 +471,7 @@ struct EllLevels {
     S.ell.v[0][0] = v;
     S.ell.row[0][0][0] = a;
     S.ell.row[0][0][1] = P.ell[2 * static_cast<size_t>(v) + 1];
-    if (a.x < 0) S.cnt[0].x = kLongRow;
+    if (a.x < 0) S.cnt[0].y = 1;
   }
   __device__ static Kept keep(Lds& S, int b, int32_t i) {
     return Kept{S.ell.v[b][i], S.ell.row[b][i][0], S.ell.row[b][i][1]};
@@ -560,7 +566,7 @@ struct EllLevels {
       if (!fresh[j] || at[j] >= kCap) continue;
       if (kLabel) S.ell.t.slot[at[j]] = static_cast<uint16_t>(slot[j]);
       store(S, b ^ 1, at[j], w[j], r[j]);
-      if (r[j][0] < 0) atomicAdd(&cnt->x, kLongRow);
+      if (r[j][0] < 0) cnt->y = 1;
     }
   }
 
@@ -577,7 +583,8 @@ struct EllLevels {
         expand_row<kMode, 2>(P, S, c, b, i, c.tid % kLanes, cnt);
     }
     __syncthreads();
-    return cnt->x;
+    const int2 n = make_int2(uniform(cnt->x), uniform(cnt->y));
+    return n.y != 0 ? kLongRow : n.x;
   }
 
   // A labelled level of at most kRows parents: a lane keeps the child it
@@ -611,10 +618,10 @@ struct EllLevels {
       load_rows<kN>(P, c, w, fresh, r);
 #pragma unroll
       for (int j = 0; j < kN; ++j)
-        if (fresh[j] && r[j][0] < 0) cnt->x = kLongRow;
+        if (fresh[j] && r[j][0] < 0) cnt->y = 1;
     }
     __syncthreads();
-    if (uniform(cnt->x) != 0) return kLongRow;
+    if (uniform(cnt->y) != 0) return kLongRow;
 #pragma unroll
     for (int j = 0; j < kN; ++j)
       if (fresh[j]) {
@@ -722,7 +729,7 @@ __device__ __forceinline__ Pass component_pass(const ComponentParams& P, Lds& S,
   __syncthreads();
   int32_t len = 1, total = 1, level = 0, near = 0;
   int l3 = 0;
-  if (uniform(S.cnt[0].x) != 0) c.state = kLong;  // the root's own row
+  if (uniform(S.cnt[0].y) != 0) c.state = kLong;  // the root's own row
   while (c.state == kRun) {
     const int b = level & 1;
     if (kMode == kProbe) c.level = level;

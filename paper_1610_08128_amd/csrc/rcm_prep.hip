@@ -53,7 +53,7 @@ __global__ void k_setup(SetupList l) {
 // the cache); longer rows raise *long_rows and are checked by k_dup_long.
 // With `ell`, the rows of at most kEllWidth entries are also copied there
 // from the registers (the traversal's fixed-stride copy); a longer row
-// raises *wide_rows and gets a first entry of -1 there.
+// raises *wide_rows and gets entries of -1 there, all of them.
 constexpr int kDupRegs = 16;
 constexpr int kDupShort = 64;
 
@@ -109,12 +109,14 @@ __global__ void k_validate_scan(int32_t n, int32_t nnz, const int32_t* __restric
           ell[2 * static_cast<size_t>(i) + 1] = make_int4(e[4], e[5], e[6], e[7]);
         } else {
           ell[2 * static_cast<size_t>(i)] = make_int4(-1, -1, -1, -1);
+          ell[2 * static_cast<size_t>(i) + 1] = make_int4(-1, -1, -1, -1);
           wide = true;
         }
       }
     } else {
       if (ell != nullptr) {
         ell[2 * static_cast<size_t>(i)] = make_int4(-1, -1, -1, -1);
+        ell[2 * static_cast<size_t>(i) + 1] = make_int4(-1, -1, -1, -1);
         wide = true;
       }
       for (int32_t k = a; k < b; ++k) {

@@ -1,0 +1,81 @@
+"""Rows longer than the row copy's eight entries, found many at a time on the
+first level that holds any: what says so must not depend on how many there
+are, nor be taken for a number of vertices.  Whole numbers throughout: every
+result must equal the oracle's."""
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_1610_08128_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+COUNTS = [127, 128, 129, 255, 256, 257, 511, 512, 768, 1023, 1024]
+
+
+def _fan(k, handle, *, rest=0, seed=None):
+    """A path of `handle` vertices into a binary tree whose last level has k,
+    each joined to nine of k more: from the path's start, k long rows come
+    together.  rest: isolated vertices beside it.  Labels 0, 1, ... from the
+    path's start unless a seed relabels them."""
+    u, v = [np.arange(handle - 1)], [np.arange(1, handle)]
+    level, n = np.array([handle - 1]), handle
+    while len(level) < k:
+        size = min(2 * len(level), k)
+        kids = np.arange(n, n + size)
+        u.append(level[np.arange(size) % len(level)])
+        v.append(kids)
+        level, n = kids, n + size
+    for d in range(9):
+        u.append(level)
+        v.append(n + (np.arange(k) + d) % k)
+    n += k + rest
+    perm = None if seed is None else np.random.default_rng(seed).permutation(n)
+    g = I.from_edges(n, np.concatenate(u), np.concatenate(v), perm=perm, name=f"fan_{k}_{handle}")
+    if seed is None:
+        long = np.flatnonzero(np.diff(g.rowptr) > 8)
+        assert len(long) == 2 * k and np.array_equal(np.sort(level), long[:k])
+    return g
+
+
+def _check(g, **opts):
+    import torch
+    from paper_1610_08128_amd import rcm
+
+    print(f"case {g.name} n={g.n} nnz={g.nnz} {opts}", flush=True)
+    want = oracle.rcm(g.n, g.rowptr, g.colidx, **opts)
+    assert want.status == oracle.OK
+    perm, iperm, st = rcm.order(torch.from_numpy(g.rowptr).cuda(),
+                                torch.from_numpy(g.colidx).cuda(), return_iperm=True, **opts)
+    assert np.array_equal(perm.cpu().numpy(), want.perm)
+    assert np.array_equal(iperm.cpu().numpy(), want.iperm)
+    assert st == want.stats
+
+
+def _check_batch(graphs, **opts):
+    import torch
+    from paper_1610_08128_amd import rcm
+
+    vo, no, rp, ci = I.concat_batch(graphs)
+    print(f"batch {[g.name for g in graphs]} {opts}", flush=True)
+    perm, stats = rcm.order_batched(vo, no, torch.from_numpy(rp).cuda(),
+                                    torch.from_numpy(ci).cuda(), **opts)
+    perm = perm.cpu().numpy()
+    for i, g in enumerate(graphs):
+        want = oracle.rcm(g.n, g.rowptr, g.colidx, **opts)
+        assert np.array_equal(perm[vo[i]:vo[i + 1]], want.perm), (i, g.name)
+        assert stats[i] == want.stats, (i, g.name)
+
+
+@pytest.mark.parametrize("k", COUNTS)
+def test_component_engine(k):
+    """Vertex 0's component (of so many levels that it is renumbered, and of
+    few), one beside it, and components of a batch.  More than 8,191 vertices
+    in a single graph, past the engines for small ones."""
+    g = _fan(k, 8200)
+    _check(g)
+    _check(_fan(k, 300, rest=8000))
+    _check(_fan(k, 300, rest=8000, seed=k), pp_variant=1, reverse_mode=1)
+    _check(I.disjoint_union([I.path(5), g, _fan(k, 60)]))
+    _check_batch([_fan(k, 40), I.grid2d(9, 7, seed=2), g, _fan(k, 300, seed=k)])
