@@ -1057,7 +1057,8 @@ struct LongLds {
   uint32_t bits[kLongRange / 32];
   int4 row[2][kLongCap][2];
   int32_t v[2][kLongCap];
-  int32_t cnt[3];
+  int2 cnt[3];                // level mod 3: size of the level being found, and 1 when a
+                              // row of it is too long for the copy
   int32_t stop;
   unsigned long long key;
 };
@@ -1068,7 +1069,7 @@ static_assert(sizeof(LongLds) <= 160 * 1024, "one work-group's LDS");
 // marked already.)
 template <int kN>
 __device__ __forceinline__ void long_reach(const ComponentParams& P, LongLds& S, int b,
-                                           int32_t len, int32_t level, int32_t* cnt) {
+                                           int32_t len, int32_t level, int2* cnt) {
   constexpr int kLanes = kEllWidth / kN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int32_t i = tid / kLanes;
@@ -1106,7 +1107,7 @@ __device__ __forceinline__ void long_reach(const ComponentParams& P, LongLds& S,
   if (all == 0) return;
   const int first = __builtin_ctzll(all);
   int base = 0;
-  if (lane == first) base = lds_add(cnt, total);
+  if (lane == first) base = lds_add(&cnt->x, total);
   base = __builtin_amdgcn_readlane(base, first);
 #pragma unroll
   for (int j = 0; j < kN; ++j) {
@@ -1118,7 +1119,7 @@ __device__ __forceinline__ void long_reach(const ComponentParams& P, LongLds& S,
     S.v[b ^ 1][at] = w[j];
     S.row[b ^ 1][at][0] = make_int4(r[j][0], r[j][1], r[j][2], r[j][3]);
     S.row[b ^ 1][at][1] = make_int4(r[j][4], r[j][5], r[j][6], r[j][7]);
-    if (r[j][0] < 0) atomicAdd(cnt, kLongRow);
+    if (r[j][0] < 0) cnt->y = 1;
   }
 }
 
@@ -1127,7 +1128,7 @@ __global__ void __launch_bounds__(kLongThreads) k_long_probe(ComponentParams P) 
   if (ld_relaxed(P.bad_csr) != 0) return;
   const int tid = threadIdx.x;
   for (int32_t i = tid; i < (P.n + 31) / 32; i += kLongThreads) S.bits[i] = 0;
-  if (tid < 3) S.cnt[tid] = 0;
+  if (tid < 3) S.cnt[tid] = make_int2(0, 0);
   __syncthreads();
   if (tid == 0) {
     const int4 lo = P.ell[0];
@@ -1144,9 +1145,9 @@ __global__ void __launch_bounds__(kLongThreads) k_long_probe(ComponentParams P) 
   int32_t len = 1, total = 1, level = 0, near = 0;
   int l3 = 0;
   while (!decline) {
-    int32_t* cnt = &S.cnt[l3];
+    int2* cnt = &S.cnt[l3];
     l3 = l3 == 2 ? 0 : l3 + 1;
-    if (tid == 0) S.cnt[l3] = 0;
+    if (tid == 0) S.cnt[l3] = make_int2(0, 0);
     const int b = level & 1;
     if (len <= kLongThreads / 8)
       long_reach<1>(P, S, b, len, level, cnt);
@@ -1155,11 +1156,12 @@ __global__ void __launch_bounds__(kLongThreads) k_long_probe(ComponentParams P) 
     else
       long_reach<4>(P, S, b, len, level, cnt);
     __syncthreads();
-    const int32_t found = uniform(*cnt);
+    const int32_t found = uniform(cnt->x);
     if (found == 0) break;
     // (a level that grows like a volume's: see component_pass)
     if (level == 3) near = found;
-    decline = found > kLongCap || (level == 7 && found * 10 >= near * P.growth);
+    decline = uniform(cnt->y) != 0 || found > kLongCap ||
+              (level == 7 && found * 10 >= near * P.growth);
     total += found;
     len = found;
     ++level;

@@ -79,3 +79,12 @@ def test_component_engine(k):
     _check(_fan(k, 300, rest=8000, seed=k), pp_variant=1, reverse_mode=1)
     _check(I.disjoint_union([I.path(5), g, _fan(k, 60)]))
     _check_batch([_fan(k, 40), I.grid2d(9, 7, seed=2), g, _fan(k, 300, seed=k)])
+
+
+@pytest.mark.parametrize("k", [127, 128, 129, 200, 255, 256, 257])
+def test_long_probe(k):
+    """The same in a graph past the component engine's range, whose first
+    structure one work-group measures (levels of at most 256 vertices)."""
+    g = _fan(k, 300, rest=1 << 19)
+    _check(g)
+    _check(g, pp_variant=1, reverse_mode=1)
