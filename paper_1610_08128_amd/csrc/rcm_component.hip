@@ -202,8 +202,7 @@ __device__ __forceinline__ int32_t lds_add(int32_t* p, int32_t x) {
 // bits are set here, and *base is the first of the places reserved for them
 // in the next level (one atomic for the wave); at[j] is entry j's.
 template <int kN>
-__device__ __forceinline__ void reserve(int32_t* cnt, const bool* fresh, int32_t extra,
-                                        int32_t* at) {
+__device__ __forceinline__ void reserve(int32_t* cnt, const bool* fresh, int32_t* at) {
   int32_t total = 0;
 #pragma unroll
   for (int j = 0; j < kN; ++j) {
@@ -213,7 +212,6 @@ __device__ __forceinline__ void reserve(int32_t* cnt, const bool* fresh, int32_t
                         __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0)));
     total += __popcll(m);
   }
-  total += extra;
   int32_t base = 0;
   if (total != 0) {
     const unsigned long long act = __ballot(true);
@@ -223,6 +221,17 @@ __device__ __forceinline__ void reserve(int32_t* cnt, const bool* fresh, int32_t
   }
 #pragma unroll
   for (int j = 0; j < kN; ++j) at[j] += base;
+}
+
+// Past kCap records a labelled level is given up: nothing more is entered, and
+// the count says so however many calls meet it (added to by each of them, it
+// took the value of another answer, and could wrap).  Returns whether this
+// level is.
+template <int kCap>
+__device__ __forceinline__ bool given_up(int32_t* cnt) {
+  const bool wide = *static_cast<volatile int32_t*>(cnt) >= kCap;
+  if (wide) atomicMax(cnt, kCap + 1);
+  return wide;
 }
 
 // Search: marks the open entries' bits; fresh[j] = this lane marked it.
@@ -353,13 +362,10 @@ struct CsrLevels {
       if (w[j] >= 0) open[j] = (S.bits[x[j] >> 5] & bit_of(x[j])) == 0;
     }
     int slot[kN];
-    int32_t extra = 0;
     if (kLabel) {
-      // past kCap records the level is given up and nothing more is entered
-      const bool wide = *static_cast<volatile int32_t*>(cnt) >= kCap;
+      const bool wide = given_up<kCap>(cnt);
 #pragma unroll
       for (int j = 0; j < kN; ++j) open[j] = open[j] && !wide;
-      if (__ballot(wide) != 0) extra = kCap;
       enter<kN>(S.csr.t, w, open, parent, fresh, slot);
     } else {
       mark<kN>(S, x, open, fresh);
@@ -377,7 +383,7 @@ struct CsrLevels {
         if (fresh[j]) P.dkey[w[j]] = distance_word(c.level + 1);
     }
     int32_t at[kN];
-    reserve<kN>(cnt, fresh, extra, at);
+    reserve<kN>(cnt, fresh, at);
 #pragma unroll
     for (int j = 0; j < kN; ++j) fresh[j] = fresh[j] && at[j] < kCap;
 #pragma unroll
@@ -537,12 +543,9 @@ struct EllLevels {
     uint32_t x[kN];
     bool open[kN], fresh[kN];
     int slot[kN];
-    int32_t extra = 0;
     entries<kN>(S, c, b, i, sub, w, x, open);
     if (kLabel) {
-      // past kCap records the level is given up and nothing more is entered
-      const bool wide = *static_cast<volatile int32_t*>(&cnt->x) >= kCap;
-      if (__ballot(wide) != 0) extra = kCap;
+      const bool wide = given_up<kCap>(&cnt->x);
       uint32_t word[kN];
 #pragma unroll
       for (int j = 0; j < kN; ++j) word[j] = S.bits[x[j] >> 5];
@@ -560,7 +563,7 @@ struct EllLevels {
       for (int j = 0; j < kN; ++j)
         if (fresh[j]) P.dkey[w[j]] = distance_word(c.level + 1);
     }
-    reserve<kN>(&cnt->x, fresh, extra, at);
+    reserve<kN>(&cnt->x, fresh, at);
 #pragma unroll
     for (int j = 0; j < kN; ++j) {
       if (!fresh[j] || at[j] >= kCap) continue;
@@ -748,7 +751,7 @@ __device__ __forceinline__ Pass component_pass(const ComponentParams& P, Lds& S,
     found = uniform(found);
     if (found == 0) break;
     if (found > c.width) {
-      c.state = found >= kLongRow ? kLong : kDecline;
+      c.state = V::kDirect && found == kLongRow ? kLong : kDecline;
       break;
     }
     if (kMode == kProbe && P.growth > 0) {
@@ -1033,8 +1036,10 @@ __global__ void __launch_bounds__(kThreads) k_component(ComponentParams P) {
       order_component(P, S, c, task, resume);
     }
     if (threadIdx.x == 0) {
-      P.declined[ti] = c.state == kDecline ? 1 : 0;
-      if (c.state == kDecline) atomicAdd(&P.counts[list], 1);
+      // (whatever was neither ordered nor refused is left to the team kernel)
+      const bool left = c.state == kDecline || c.state == kLong;
+      P.declined[ti] = left ? 1 : 0;
+      if (left) atomicAdd(&P.counts[list], 1);
       if (c.state == kAsym) flag_error(P.gctl, RCM_ERR_NOT_SYMMETRIC);
     }
     if (c.state == kAbort) return;

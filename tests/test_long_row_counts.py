@@ -1,7 +1,9 @@
-"""Rows longer than the row copy's eight entries, found many at a time on the
-first level that holds any: what says so must not depend on how many there
-are, nor be taken for a number of vertices.  Whole numbers throughout: every
-result must equal the oracle's."""
+"""What a level of the component engine says beside its number of vertices: a
+row longer than the row copy's eight entries, found many at a time on the
+first level that holds any; more children than a level may have, met by many
+rows.  Neither must depend on how many there are, nor be taken for a number of
+vertices or for each other.  Whole numbers throughout: every result must equal
+the oracle's."""
 
 import numpy as np
 import pytest
@@ -88,3 +90,40 @@ def test_long_probe(k):
     g = _fan(k, 300, rest=1 << 19)
     _check(g)
     _check(g, pp_variant=1, reverse_mode=1)
+
+
+def _wide_from_one_side(children, tail, seed=None):
+    """1,000 parents joined to the same children: through the vertex that
+    half the children hang on, no level is wider than the parents or half the
+    children; through the one the parents hang on, all children are a level.
+    Label 0 behind the first, a longer path away from it than the other's."""
+    parents = 1000
+    half = children // 2
+    x, y = tail, 5  # path 0 .. x - 1 (0 next to the first vertex), path of y
+    side, top = x, x + 1
+    a = np.arange(parents) + x + 2
+    b = np.arange(children) + x + 2 + parents
+    far = np.arange(y) + x + 2 + parents + children
+    u = [np.arange(x - 1), [0], np.full(half, side), np.repeat(a, children), a, [top], far[:-1]]
+    v = [np.arange(1, x), [side], b[:half], np.tile(b, parents), np.full(parents, top), [far[0]],
+         far[1:]]
+    n = int(far[-1]) + 1
+    perm = None
+    if seed is not None:  # label 0 stays
+        perm = np.concatenate([[0], 1 + np.random.default_rng(seed).permutation(n - 1)])
+    return I.from_edges(n, np.concatenate([np.asarray(e, dtype=np.int64) for e in u]),
+                        np.concatenate([np.asarray(e, dtype=np.int64) for e in v]), perm=perm,
+                        name=f"wide_{children}")
+
+
+@pytest.mark.parametrize("children", [2000, 2048, 2049, 2100])
+def test_only_the_labelled_level_is_wide(children):
+    """The searches see half the children at once, the labelled BFS all of
+    them, in rows of so many entries that 16,000 wave calls meet the level
+    that is given up: the component must go to the team kernel.  Vertex 0's
+    component, one beside it, and one of a batch."""
+    g = _wide_from_one_side(children, 9000)
+    _check(g)
+    _check(_wide_from_one_side(children, 9000, seed=children))
+    _check(I.disjoint_union([I.path(5), g]), reverse_mode=1)
+    _check_batch([I.path(9), _wide_from_one_side(children, 100), I.grid2d(9, 7, seed=2)])
