@@ -153,8 +153,9 @@ k_move_rows(int32_t n, int32_t nnz, const int32_t* __restrict__ colidx,
     c[u] = colidx[e];
     if (kVals) x[u] = vals[e];
   }
+  // (an empty row has loaded some entry, which can lie past the matrix's own)
 #pragma unroll
-  for (int u = 0; u < kUnroll; ++u) c[u] = iperm[c[u]];
+  for (int u = 0; u < kUnroll; ++u) c[u] = iperm[len[u] > 0 ? c[u] : 0];
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
     if (sub >= len[u]) c[u] = kPast;

@@ -209,3 +209,33 @@ def test_gpu_permute_and_spmv_row_lengths(n, values):
         total = oracle.spmv(g.n, g.rowptr, g.colidx, np.abs(x),
                             np.abs(vals) if values else None)
         assert np.all(np.abs(y - exact) <= 2 * lengths * 2.0**-53 * total)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [1, 127, 129, 1000])
+@pytest.mark.parametrize("values", [True, False])
+def test_gpu_permute_arrays_longer_than_the_matrix(n, values):
+    """Column and value arrays with room past the matrix's last entry, whose
+    words there are no columns: no row may look at them, an empty one at the
+    matrix's end least of all."""
+    import torch
+    from paper_1610_08128_amd import apply
+
+    rng = np.random.default_rng(n)
+    lengths = rng.integers(0, min(n, 20) + 1, n)
+    lengths[-(n // 3 + 1):] = 0
+    g = _rows_of(lengths, n)
+    vals = rng.standard_normal(g.nnz)
+    perm = rng.permutation(n).astype(np.int32)
+    iperm = np.argsort(perm).astype(np.int32)
+    want_rp, want_ci, want_v = oracle.permute_csr(n, g.rowptr, g.colidx, perm, vals)
+    room = 37
+    ci = np.concatenate([g.colidx, np.full(room, 1 << 30, np.int32)])
+    v = np.concatenate([vals, np.full(room, np.nan)])
+    brp, bci, bv = apply.permute(
+        torch.from_numpy(g.rowptr).cuda(), torch.from_numpy(ci).cuda(),
+        torch.from_numpy(perm).cuda(), torch.from_numpy(iperm).cuda(),
+        torch.from_numpy(v).cuda() if values else None)
+    assert np.array_equal(brp.cpu().numpy(), want_rp)
+    assert np.array_equal(bci.cpu().numpy()[:g.nnz], want_ci)
+    assert not values or np.array_equal(bv.cpu().numpy()[:g.nnz], want_v)
