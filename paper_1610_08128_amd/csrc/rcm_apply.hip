@@ -12,8 +12,6 @@
 
 #include "rcm_apply.h"
 
-#include <algorithm>
-
 #include <hip/hip_runtime.h>
 
 #include "rcm_common.hpp"
@@ -34,12 +32,14 @@ inline int grid_for(int64_t work, int threads, int max_blocks = 8192) {
 
 // Workspace regions of rcm_permute.
 struct ApplyLayout {
-  size_t deg, begin, blk, counts, sort, total;
+  size_t deg, blk, counts, begin, sort, total;
+  bool begins;  // there is room for the rows' begins
 };
 
-// The workspace asked for has room for a copy of the columns and values as
-// well, although rows are sorted where they are read: the size is part of the
-// interface, so a workspace below it is refused as it always was.
+// The workspace's size is part of the interface: room for a copy of the
+// columns and values, although rows are sorted where they are read.  The
+// numbers of medium and long rows and the rows' begins lie there.  A matrix of
+// so few entries that the begins do not fit goes without them.
 ApplyLayout apply_layout(int32_t n, int64_t nnz, bool with_values) {
   ApplyLayout L{};
   size_t off = 0;
@@ -50,12 +50,13 @@ ApplyLayout apply_layout(int32_t n, int64_t nnz, bool with_values) {
   };
   const size_t N = static_cast<size_t>(n), M = static_cast<size_t>(nnz);
   L.deg = take(4 * N);
-  L.begin = take(4 * N);
   L.blk = take(4 * (N / 4096 + 2));
-  L.counts = take(8);     // medium and long rows
-  L.sort = take(8 * M);  // (column, position) pairs of rows too long for LDS
   const size_t copies = align_up(4 * M) + (with_values ? align_up(8 * M) : 0);
-  L.total = std::max(off, off - align_up(4 * N) - align_up(8) + copies);
+  L.counts = take(copies);  // (nothing without an entry)
+  L.begin = L.counts + align_up(8);
+  L.begins = align_up(8) + 4 * N <= copies;
+  L.sort = take(8 * M);  // (column, position) pairs of rows too long for LDS
+  L.total = off;
   return L;
 }
 
@@ -73,19 +74,31 @@ inline unsigned xcd_grid(int64_t tiles) {
   return static_cast<unsigned>((tiles + kXcds - 1) / kXcds * kXcds);
 }
 
-// Row k of B starts at begin[k] in A and has deg[k] entries.
+// Row k of B starts at begin[k] in A (begin null: not kept) and has deg[k]
+// entries; counts (null without any entry) starts at 0.
 __global__ void k_new_degrees(int32_t n, const int32_t* __restrict__ rowptr,
                               const int32_t* __restrict__ perm, int32_t* __restrict__ deg,
                               int32_t* __restrict__ begin, int32_t* __restrict__ counts) {
   const int32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < 2) counts[t] = 0;
+  if (counts != nullptr && t < 2) counts[t] = 0;
   for (int32_t k = t; k < n; k += gridDim.x * blockDim.x) {
     const int32_t v = perm[k];
     const int32_t a = rowptr[v];
     deg[k] = rowptr[v + 1] - a;
-    begin[k] = a;
+    if (begin != nullptr) begin[k] = a;
   }
 }
+
+// Where row k of B begins in A: kept, or by way of the order.
+template <bool kKept>
+struct Begins {
+  const int32_t* kept;
+  const int32_t* rowptr;
+  const int32_t* perm;
+  __device__ __forceinline__ int32_t operator[](int32_t k) const {
+    return kKept ? kept[k] : rowptr[perm[k]];
+  }
+};
 
 // Row k of B: row perm[k] of A with its columns renamed by iperm, sorted
 // (equal columns in input order).  Eight lanes take a row of at most
@@ -121,10 +134,10 @@ __device__ __forceinline__ int group_rank(int32_t c, int sub) {
   return r;
 }
 
-template <bool kVals>
+template <bool kVals, bool kKept>
 __global__ void __launch_bounds__(kThreads)
 k_move_rows(int32_t n, int32_t nnz, const int32_t* __restrict__ colidx,
-            const double* __restrict__ vals, const int32_t* __restrict__ begin,
+            const double* __restrict__ vals, Begins<kKept> begin,
             const int32_t* __restrict__ iperm, const int32_t* __restrict__ rowptr_out,
             int32_t* __restrict__ colidx_out, double* __restrict__ vals_out,
             int32_t* __restrict__ list, int32_t* __restrict__ counts) {
@@ -202,9 +215,10 @@ k_move_rows(int32_t n, int32_t nnz, const int32_t* __restrict__ colidx,
 
 // The medium rows: a wave each, an entry a lane, ranked against the others
 // by broadcasts.
+template <bool kKept>
 __global__ void __launch_bounds__(kThreads)
 k_sort_medium_rows(const int32_t* __restrict__ colidx, const double* __restrict__ vals,
-                   const int32_t* __restrict__ begin, const int32_t* __restrict__ iperm,
+                   Begins<kKept> begin, const int32_t* __restrict__ iperm,
                    const int32_t* __restrict__ rowptr_out, const int32_t* __restrict__ list,
                    const int32_t* __restrict__ counts, int32_t* __restrict__ colidx_out,
                    double* __restrict__ vals_out) {
@@ -265,9 +279,10 @@ __device__ __forceinline__ void bitonic_pairs(unsigned long long* a, int32_t len
   }
 }
 
+template <bool kKept>
 __global__ void __launch_bounds__(kLongThreads)
 k_sort_long_rows(int32_t n, const int32_t* __restrict__ colidx, const double* __restrict__ vals,
-                 const int32_t* __restrict__ begin, const int32_t* __restrict__ iperm,
+                 Begins<kKept> begin, const int32_t* __restrict__ iperm,
                  const int32_t* __restrict__ rowptr_out, const int32_t* __restrict__ list,
                  const int32_t* __restrict__ counts, unsigned long long* __restrict__ pairs,
                  int32_t* __restrict__ colidx_out, double* __restrict__ vals_out) {
@@ -386,6 +401,36 @@ k_spmv(int32_t n, const int32_t* __restrict__ rowptr, const int32_t* __restrict_
   }
 }
 
+// The rows' kernels of rcm_permute.
+template <bool kKept>
+hipError_t launch_moves(int32_t n, int64_t nnz, const int32_t* colidx, const double* vals,
+                        Begins<kKept> begin, const int32_t* iperm, const int32_t* rowptr_out,
+                        int32_t* colidx_out, double* vals_out, int32_t* list, int32_t* counts,
+                        unsigned long long* pairs, hipStream_t s) {
+  const unsigned blocks = xcd_grid((static_cast<int64_t>(n) + kTileRows - 1) / kTileRows);
+  const int32_t m = static_cast<int32_t>(nnz);
+  if (vals)
+    k_move_rows<true, kKept><<<blocks, kThreads, 0, s>>>(
+        n, m, colidx, vals, begin, iperm, rowptr_out, colidx_out, vals_out, list, counts);
+  else
+    k_move_rows<false, kKept><<<blocks, kThreads, 0, s>>>(
+        n, m, colidx, vals, begin, iperm, rowptr_out, colidx_out, vals_out, list, counts);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  // (a row needs more than kShortRow of the nnz entries to be listed)
+  const int64_t most = nnz / (kShortRow + 1);
+  if (most > 0) {
+    k_sort_medium_rows<<<grid_for(most, kThreads / 64, 2048), kThreads, 0, s>>>(
+        colidx, vals, begin, iperm, rowptr_out, list, counts, colidx_out, vals_out);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  if (nnz > kMediumRow)
+    k_sort_long_rows<<<grid_for(nnz / (kMediumRow + 1), 1, 1024), kLongThreads, 0, s>>>(
+        n, colidx, vals, begin, iperm, rowptr_out, list, counts, pairs, colidx_out, vals_out);
+  return hipGetLastError();
+}
+
 }  // namespace
 }  // namespace rcm
 
@@ -412,38 +457,25 @@ rcm_status rcm_permute(int32_t n, int64_t nnz, const int32_t* rowptr, const int3
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
   int32_t* deg = reinterpret_cast<int32_t*>(ws + L.deg);
-  int32_t* begin = reinterpret_cast<int32_t*>(ws + L.begin);
+  int32_t* begin = L.begins ? reinterpret_cast<int32_t*>(ws + L.begin) : nullptr;
   int32_t* blk = reinterpret_cast<int32_t*>(ws + L.blk);
   unsigned long long* pairs = reinterpret_cast<unsigned long long*>(ws + L.sort);
   // the degrees are scanned before the rows move: deg then takes the lists of
   // medium and long rows
   int32_t* list = deg;
-  int32_t* counts = reinterpret_cast<int32_t*>(ws + L.counts);
+  int32_t* counts = nnz > 0 ? reinterpret_cast<int32_t*>(ws + L.counts) : nullptr;
   k_new_degrees<<<grid_for(n, kThreads), kThreads, 0, s>>>(n, rowptr, perm, deg, begin, counts);
   if (hipGetLastError() != hipSuccess) return RCM_ERR_HIP;
   if (launch_exclusive_scan(deg, rowptr_out, n, blk, rowptr_out + n, s) != hipSuccess)
     return RCM_ERR_HIP;
   if (nnz == 0) return RCM_OK;
-  const unsigned blocks = xcd_grid((static_cast<int64_t>(n) + kTileRows - 1) / kTileRows);
-  const int32_t m = static_cast<int32_t>(nnz);
-  if (vals)
-    k_move_rows<true><<<blocks, kThreads, 0, s>>>(n, m, colidx, vals, begin, iperm, rowptr_out,
-                                                  colidx_out, vals_out, list, counts);
-  else
-    k_move_rows<false><<<blocks, kThreads, 0, s>>>(n, m, colidx, vals, begin, iperm, rowptr_out,
-                                                   colidx_out, vals_out, list, counts);
-  if (hipGetLastError() != hipSuccess) return RCM_ERR_HIP;
-  // (a row needs more than kShortRow of the nnz entries to be listed)
-  const int64_t most = nnz / (kShortRow + 1);
-  if (most > 0) {
-    k_sort_medium_rows<<<grid_for(most, kThreads / 64, 2048), kThreads, 0, s>>>(
-        colidx, vals, begin, iperm, rowptr_out, list, counts, colidx_out, vals_out);
-    if (hipGetLastError() != hipSuccess) return RCM_ERR_HIP;
-  }
-  if (nnz > kMediumRow)
-    k_sort_long_rows<<<grid_for(nnz / (kMediumRow + 1), 1, 1024), kLongThreads, 0, s>>>(
-        n, colidx, vals, begin, iperm, rowptr_out, list, counts, pairs, colidx_out, vals_out);
-  return hipGetLastError() == hipSuccess ? RCM_OK : RCM_ERR_HIP;
+  auto move = [&](auto begin) {
+    return launch_moves(n, nnz, colidx, vals, begin, iperm, rowptr_out, colidx_out, vals_out,
+                        list, counts, pairs, s);
+  };
+  const hipError_t e = L.begins ? move(Begins<true>{begin, rowptr, perm})
+                                : move(Begins<false>{nullptr, rowptr, perm});
+  return e == hipSuccess ? RCM_OK : RCM_ERR_HIP;
 }
 
 rcm_status rcm_spmv(int32_t n, const int32_t* rowptr, const int32_t* colidx, const double* vals,

@@ -239,3 +239,61 @@ def test_gpu_permute_arrays_longer_than_the_matrix(n, values):
     assert np.array_equal(brp.cpu().numpy(), want_rp)
     assert np.array_equal(bci.cpu().numpy()[:g.nnz], want_ci)
     assert not values or np.array_equal(bv.cpu().numpy()[:g.nnz], want_v)
+
+
+def _permute_workspace(n, nnz, values):
+    """The interface's size: degrees, the scan's sums, a copy of the columns
+    and of the values, sort pairs, each rounded up to 256 bytes."""
+    up = lambda b: (b + 255) // 256 * 256  # noqa: E731
+    return (up(4 * n) + up(4 * (n // 4096 + 2)) + up(4 * nnz) + (up(8 * nnz) if values else 0)
+            + up(8 * nnz))
+
+
+@pytest.mark.parametrize("n", [1, 64, 4095, 4096, 100_000, 2**31 - 1])
+def test_permute_workspace_is_the_interfaces(n):
+    from paper_1610_08128_amd import apply
+
+    for nnz in (0, 1, 63, n // 3, n - 1, n, n + 63, n + 64, n + 65, 7 * n, 2**31 - 2):
+        if nnz >= 2**31 - 1:
+            continue
+        for values in (False, True):
+            assert apply.permute_workspace_bytes(n, nnz, values) == \
+                _permute_workspace(n, nnz, values)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("entries", [0, 1, 70, 1000, 9000, 12_000, 13_000, 37_000])
+@pytest.mark.parametrize("values", [True, False])
+def test_gpu_permute_few_entries(entries, values):
+    """Fewer entries than rows, around the numbers at which the workspace has
+    no room for the rows' begins; short, medium and long rows among them, and
+    nothing behind the workspace touched."""
+    import torch
+    from paper_1610_08128_amd import apply
+
+    n = 12_500
+    rng = np.random.default_rng(entries)
+    lengths = np.zeros(n, np.int64)
+    left = entries
+    for k in (8200, 300, 40, 17, 9):
+        if left >= k:
+            lengths[rng.integers(0, n // 2)] = k
+            left = entries - int(lengths.sum())
+    lengths[n // 2:] += rng.multinomial(left, np.full(n - n // 2, 1 / (n - n // 2)))
+    g = _rows_of(lengths, entries)
+    assert g.nnz == entries
+    vals = rng.standard_normal(entries)
+    perm = rng.permutation(n).astype(np.int32)
+    iperm = np.argsort(perm).astype(np.int32)
+    want_rp, want_ci, want_v = oracle.permute_csr(n, g.rowptr, g.colidx, perm, vals)
+    size = _permute_workspace(n, entries, values)
+    buf = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    args = [torch.from_numpy(a).cuda() for a in (g.rowptr, g.colidx, perm, iperm)]
+    v = torch.from_numpy(vals).cuda() if values else None
+    with pytest.raises(Exception):
+        apply.permute(*args, v, workspace=buf[:size - 1])
+    brp, bci, bv = apply.permute(*args, v, workspace=buf[:size])
+    assert np.array_equal(brp.cpu().numpy(), want_rp)
+    assert np.array_equal(bci.cpu().numpy(), want_ci)
+    assert not values or np.array_equal(bv.cpu().numpy(), want_v)
+    assert bool((buf[size:] == 0x5A).all())
