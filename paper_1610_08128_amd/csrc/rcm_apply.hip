@@ -136,7 +136,7 @@ __device__ __forceinline__ int group_rank(int32_t c, int sub) {
 
 template <bool kVals, bool kKept>
 __global__ void __launch_bounds__(kThreads)
-k_move_rows(int32_t n, int32_t nnz, const int32_t* __restrict__ colidx,
+k_move_rows(int32_t n, const int32_t* __restrict__ colidx,
             const double* __restrict__ vals, Begins<kKept> begin,
             const int32_t* __restrict__ iperm, const int32_t* __restrict__ rowptr_out,
             int32_t* __restrict__ colidx_out, double* __restrict__ vals_out,
@@ -159,16 +159,19 @@ k_move_rows(int32_t n, int32_t nnz, const int32_t* __restrict__ colidx,
     o[u] = rowptr_out[kk];
     len[u] = k < n ? rowptr_out[kk + 1] - o[u] : 0;
   }
-  // (indices clamped into the arrays, so that all loads are issued at once)
+  // (indices clamped into the matrix's entries, behind which the arrays may hold
+  // anything, so that all loads are issued at once)
+  const int32_t last = rowptr_out[n] - 1;
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
-    const int32_t e = min(a[u] + min(sub, max(len[u] - 1, 0)), nnz - 1);
+    const uint32_t e = min(static_cast<uint32_t>(a[u] + min(sub, max(len[u] - 1, 0))),
+                           static_cast<uint32_t>(last));
     c[u] = colidx[e];
     if (kVals) x[u] = vals[e];
   }
-  // (an empty row has loaded some entry, which can lie past the matrix's own)
+  if (last < 0) return;
 #pragma unroll
-  for (int u = 0; u < kUnroll; ++u) c[u] = iperm[len[u] > 0 ? c[u] : 0];
+  for (int u = 0; u < kUnroll; ++u) c[u] = iperm[c[u]];
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
     if (sub >= len[u]) c[u] = kPast;
@@ -408,13 +411,12 @@ hipError_t launch_moves(int32_t n, int64_t nnz, const int32_t* colidx, const dou
                         int32_t* colidx_out, double* vals_out, int32_t* list, int32_t* counts,
                         unsigned long long* pairs, hipStream_t s) {
   const unsigned blocks = xcd_grid((static_cast<int64_t>(n) + kTileRows - 1) / kTileRows);
-  const int32_t m = static_cast<int32_t>(nnz);
   if (vals)
     k_move_rows<true, kKept><<<blocks, kThreads, 0, s>>>(
-        n, m, colidx, vals, begin, iperm, rowptr_out, colidx_out, vals_out, list, counts);
+        n, colidx, vals, begin, iperm, rowptr_out, colidx_out, vals_out, list, counts);
   else
     k_move_rows<false, kKept><<<blocks, kThreads, 0, s>>>(
-        n, m, colidx, vals, begin, iperm, rowptr_out, colidx_out, vals_out, list, counts);
+        n, colidx, vals, begin, iperm, rowptr_out, colidx_out, vals_out, list, counts);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // (a row needs more than kShortRow of the nnz entries to be listed)
