@@ -317,20 +317,22 @@ k_sort_long_rows(int32_t n, const int32_t* __restrict__ colidx, const double* __
 // One batch of eight entries of each of the group's rows: entry `off` + lane,
 // rows [first, end).  Branch-free, so that every load is issued before the
 // first is waited for: past its end a row's last entry is read again (no row
-// is empty) and not added.
+// is empty) and not added.  (Unsigned: the last rows of a matrix of nearly
+// 2^31 entries reach past that.)
 template <bool kVals>
 __device__ __forceinline__ void load_batch(const int32_t* __restrict__ colidx,
-                                           const double* __restrict__ vals, const int32_t* at,
-                                           const int32_t* end, int off, int32_t* c, double* w) {
+                                           const double* __restrict__ vals, const uint32_t* at,
+                                           const uint32_t* end, uint32_t off, int32_t* c,
+                                           double* w) {
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
-    const int32_t e = min(at[u] + off, end[u] - 1);
+    const uint32_t e = min(at[u] + off, end[u] - 1u);
     c[u] = colidx[e];
     w[u] = kVals ? vals[e] : 1.0;
   }
 }
-__device__ __forceinline__ void add_batch(const double* __restrict__ x, const int32_t* at,
-                                          const int32_t* end, int off, const int32_t* c,
+__device__ __forceinline__ void add_batch(const double* __restrict__ x, const uint32_t* at,
+                                          const uint32_t* end, uint32_t off, const int32_t* c,
                                           const double* w, double* s) {
   double g[kUnroll];
 #pragma unroll
@@ -355,21 +357,22 @@ __global__ void __launch_bounds__(kThreads)
 k_spmv(int32_t n, const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
        const double* __restrict__ vals, const double* __restrict__ x, double* __restrict__ y) {
   const int64_t r0 = xcd_tile() * kTileRows + threadIdx.x / kGroup;
-  const int lane = threadIdx.x % kGroup;
-  int32_t at[kUnroll], end[kUnroll];
+  const uint32_t lane = threadIdx.x % kGroup;
+  uint32_t at[kUnroll], end[kUnroll];
   double s[kUnroll];
   int32_t longest = 0, shortest = 1;
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
     const int64_t r = r0 + u * kGroups;
     const int32_t rr = r < n ? static_cast<int32_t>(r) : n - 1;
-    at[u] = rowptr[rr];
-    end[u] = rowptr[rr + 1];
+    at[u] = static_cast<uint32_t>(rowptr[rr]);
+    end[u] = static_cast<uint32_t>(rowptr[rr + 1]);
   }
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
-    longest = max(longest, end[u] - at[u]);
-    shortest = min(shortest, end[u] - at[u]);
+    const int32_t len = static_cast<int32_t>(end[u] - at[u]);
+    longest = max(longest, len);
+    shortest = min(shortest, len);
     at[u] += lane;
     s[u] = 0.0;
   }
@@ -377,7 +380,7 @@ k_spmv(int32_t n, const int32_t* __restrict__ rowptr, const int32_t* __restrict_
     int32_t c[kUnroll], c2[kUnroll];
     double w[kUnroll], w2[kUnroll];
     load_batch<kVals>(colidx, vals, at, end, 0, c, w);
-    for (int off = 0;;) {
+    for (int32_t off = 0;;) {
       const bool more = __any(off + kGroup < longest);
       if (more) load_batch<kVals>(colidx, vals, at, end, off + kGroup, c2, w2);
       add_batch(x, at, end, off, c, w, s);
@@ -392,7 +395,7 @@ k_spmv(int32_t n, const int32_t* __restrict__ rowptr, const int32_t* __restrict_
   } else {
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u)
-      for (int32_t e = at[u]; e < end[u]; e += kGroup)
+      for (uint32_t e = at[u]; e < end[u]; e += kGroup)
         s[u] = fma(kVals ? vals[e] : 1.0, x[colidx[e]], s[u]);
   }
 #pragma unroll

@@ -213,7 +213,9 @@ k_validate_long(int32_t n, int32_t nnz, const int32_t* __restrict__ rowptr,
 #pragma unroll
     for (int q = 0; q < kBatch; ++q) {
       const bool sound = begin[q] >= 0 && end[q] > begin[q] && end[q] <= nnz;
-      const int32_t k0 = begin[q] + sub, k1 = k0 + kLanes, top = end[q] - 1;
+      // (unsigned: the last rows of nearly 2^31 entries reach past that)
+      const uint32_t k0 = static_cast<uint32_t>(begin[q]) + static_cast<uint32_t>(sub);
+      const uint32_t k1 = k0 + kLanes, top = static_cast<uint32_t>(end[q]) - 1u;
       e0[q] = nnz > 0 ? static_cast<uint32_t>(colidx[sound ? (k0 < top ? k0 : top) : 0]) : 0u;
       e1[q] = nnz > 0 ? static_cast<uint32_t>(colidx[sound ? (k1 < top ? k1 : top) : 0]) : 0u;
     }
@@ -416,8 +418,10 @@ k_check_segments(int32_t n, int32_t nnz, const int32_t* __restrict__ rowptr,
     }
 #pragma unroll
     for (int j = 0; j < kRows; ++j) {
-      const int32_t k = a[j] + sub;
-      c[j] = nnz > 0 ? colidx[k < b[j] ? k : a[j]] : 0;
+      // (unsigned: the last rows of nearly 2^31 entries reach past that)
+      const uint32_t k = static_cast<uint32_t>(a[j]) + static_cast<uint32_t>(sub);
+      c[j] = nnz > 0 ? colidx[k < static_cast<uint32_t>(b[j]) ? k : static_cast<uint32_t>(a[j])]
+                     : 0;
     }
 #pragma unroll
     for (int j = 0; j < kRows; ++j) {
@@ -425,7 +429,8 @@ k_check_segments(int32_t n, int32_t nnz, const int32_t* __restrict__ rowptr,
       while (s + 1 < nseg && i >= seg_off[s + 1]) ++s;
       const int32_t lo = seg_off[s], hi = seg_off[s + 1];
       bad |= b[j] > a[j] && (c[j] < lo || c[j] >= hi);
-      for (int32_t k = a[j] + sub + kRowLanes; k < b[j]; k += kRowLanes)
+      for (uint32_t k = static_cast<uint32_t>(a[j]) + static_cast<uint32_t>(sub + kRowLanes);
+           k < static_cast<uint32_t>(b[j]); k += kRowLanes)
         bad |= colidx[k] < lo || colidx[k] >= hi;
     }
   }
@@ -932,8 +937,10 @@ k_beta_after(int32_t n, int32_t nnz, const int32_t* __restrict__ rowptr,
   const int64_t per = gridDim.x / kXcds;
   const int64_t tile = static_cast<int64_t>(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
   const int64_t k0 = tile * kBetaTile + threadIdx.x / kBetaLanes;
-  const int sub = threadIdx.x % kBetaLanes;
-  int32_t a[kBetaUnroll], b[kBetaUnroll], f[kBetaUnroll], c[kBetaUnroll];
+  const uint32_t sub = threadIdx.x % kBetaLanes;
+  // (unsigned: the last rows of nearly 2^31 entries reach past that)
+  uint32_t a[kBetaUnroll], b[kBetaUnroll];
+  int32_t f[kBetaUnroll], c[kBetaUnroll];
 #pragma unroll
   for (int u = 0; u < kBetaUnroll; ++u) {
     const int64_t k = k0 + u * kBetaGroups;
@@ -941,8 +948,8 @@ k_beta_after(int32_t n, int32_t nnz, const int32_t* __restrict__ rowptr,
   }
 #pragma unroll
   for (int u = 0; u < kBetaUnroll; ++u) {
-    a[u] = kEll ? 0 : rowptr[c[u]];
-    b[u] = kEll ? kBetaLanes : rowptr[c[u] + 1];
+    a[u] = kEll ? 0u : static_cast<uint32_t>(rowptr[c[u]]);
+    b[u] = kEll ? kBetaLanes : static_cast<uint32_t>(rowptr[c[u] + 1]);
   }
   if (kEll) {
 #pragma unroll
@@ -955,7 +962,7 @@ k_beta_after(int32_t n, int32_t nnz, const int32_t* __restrict__ rowptr,
     // entry, which is not used)
 #pragma unroll
     for (int u = 0; u < kBetaUnroll; ++u)
-      c[u] = colidx[min(max(min(a[u] + sub, b[u] - 1), 0), nnz - 1)];
+      c[u] = colidx[min(min(a[u] + sub, b[u] - 1u), static_cast<uint32_t>(nnz) - 1u)];
 #pragma unroll
     for (int u = 0; u < kBetaUnroll; ++u) c[u] = iperm[c[u]];
   }
@@ -964,7 +971,7 @@ k_beta_after(int32_t n, int32_t nnz, const int32_t* __restrict__ rowptr,
     const int64_t k = k0 + u * kBetaGroups;
     f[u] = static_cast<int32_t>(k < n ? k : n - 1);
     if (a[u] + sub < b[u]) f[u] = min(f[u], c[u]);
-    for (int32_t e = a[u] + kBetaLanes + sub; !kEll && e < b[u]; e += kBetaLanes)
+    for (uint32_t e = a[u] + kBetaLanes + sub; !kEll && e < b[u]; e += kBetaLanes)
       f[u] = min(f[u], iperm[colidx[e]]);
 #pragma unroll
     for (int m = 1; m < kBetaLanes; m <<= 1)
