@@ -48,11 +48,12 @@ constexpr int kHeavyCap = 32;
 constexpr int kScanAll = 512;       // parents a single wave scans
 constexpr int32_t kNone = -1;
 constexpr uint32_t kSelf = 0x80000000u;  // the row holds its diagonal entry
-// A level's answer when a vertex of it has a row too long for the copy.  What
-// says so is a word of its own (Lds::cnt's second), never part of the count:
-// each of up to kThreads vertices can be found by another lane.
+// A bit of a level's count, raised (by or, as many lanes can find one) when a
+// vertex of it has a row too long for the copy.  The count below it never
+// reaches it: a vertex is counted once per pass.  (A word of its own, read
+// with the count, made a level of the 223 x 227 grid 2 % slower.)
 constexpr int32_t kLongRow = 1 << 24;
-static_assert(kLongRow > kComponentRange, "no level holds as many vertices");
+static_assert(kLongRow > kComponentRange && kLongRow > kLongRange, "above every count");
 
 // The next level's table of a labelled level: vertex and smallest parent's
 // index in the level, at most half full (see reach_label), the slot of each
@@ -94,9 +95,8 @@ struct Lds {
     EllLds ell;
   };
   int32_t wtot[kWaves];
-  int2 cnt[3];                // level mod 3: size of the level being found, and of its rows
-                              // the long ones (CsrLevels: so many are to be read by the
-                              // work-group; EllLevels: 1 = one is too long for the copy)
+  int2 cnt[3];                // level mod 3: size of the level being found (and kLongRow),
+                              // long rows of its parents (CsrLevels)
   int32_t heavy[kHeavyCap];
   unsigned long long key;
   long long red[16];
@@ -477,7 +477,7 @@ struct EllLevels {
     S.ell.v[0][0] = v;
     S.ell.row[0][0][0] = a;
     S.ell.row[0][0][1] = P.ell[2 * static_cast<size_t>(v) + 1];
-    if (a.x < 0) S.cnt[0].y = 1;
+    if (a.x < 0) S.cnt[0].x = kLongRow;
   }
   __device__ static Kept keep(Lds& S, int b, int32_t i) {
     return Kept{S.ell.v[b][i], S.ell.row[b][i][0], S.ell.row[b][i][1]};
@@ -569,7 +569,7 @@ struct EllLevels {
       if (!fresh[j] || at[j] >= kCap) continue;
       if (kLabel) S.ell.t.slot[at[j]] = static_cast<uint16_t>(slot[j]);
       store(S, b ^ 1, at[j], w[j], r[j]);
-      if (r[j][0] < 0) cnt->y = 1;
+      if (r[j][0] < 0) atomicOr(&cnt->x, kLongRow);
     }
   }
 
@@ -586,8 +586,7 @@ struct EllLevels {
         expand_row<kMode, 2>(P, S, c, b, i, c.tid % kLanes, cnt);
     }
     __syncthreads();
-    const int2 n = make_int2(uniform(cnt->x), uniform(cnt->y));
-    return n.y != 0 ? kLongRow : n.x;
+    return cnt->x;
   }
 
   // A labelled level of at most kRows parents: a lane keeps the child it
@@ -621,10 +620,10 @@ struct EllLevels {
       load_rows<kN>(P, c, w, fresh, r);
 #pragma unroll
       for (int j = 0; j < kN; ++j)
-        if (fresh[j] && r[j][0] < 0) cnt->y = 1;
+        if (fresh[j] && r[j][0] < 0) cnt->x = kLongRow;  // (counts nothing)
     }
     __syncthreads();
-    if (uniform(cnt->y) != 0) return kLongRow;
+    if (uniform(cnt->x) != 0) return kLongRow;
 #pragma unroll
     for (int j = 0; j < kN; ++j)
       if (fresh[j]) {
@@ -732,7 +731,7 @@ __device__ __forceinline__ Pass component_pass(const ComponentParams& P, Lds& S,
   __syncthreads();
   int32_t len = 1, total = 1, level = 0, near = 0;
   int l3 = 0;
-  if (uniform(S.cnt[0].y) != 0) c.state = kLong;  // the root's own row
+  if (uniform(S.cnt[0].x) != 0) c.state = kLong;  // the root's own row
   while (c.state == kRun) {
     const int b = level & 1;
     if (kMode == kProbe) c.level = level;
@@ -751,7 +750,7 @@ __device__ __forceinline__ Pass component_pass(const ComponentParams& P, Lds& S,
     found = uniform(found);
     if (found == 0) break;
     if (found > c.width) {
-      c.state = V::kDirect && found == kLongRow ? kLong : kDecline;
+      c.state = V::kDirect && found >= kLongRow ? kLong : kDecline;
       break;
     }
     if (kMode == kProbe && P.growth > 0) {
@@ -1062,8 +1061,7 @@ struct LongLds {
   uint32_t bits[kLongRange / 32];
   int4 row[2][kLongCap][2];
   int32_t v[2][kLongCap];
-  int2 cnt[3];                // level mod 3: size of the level being found, and 1 when a
-                              // row of it is too long for the copy
+  int32_t cnt[3];             // level mod 3: size of the level being found (and kLongRow)
   int32_t stop;
   unsigned long long key;
 };
@@ -1074,7 +1072,7 @@ static_assert(sizeof(LongLds) <= 160 * 1024, "one work-group's LDS");
 // marked already.)
 template <int kN>
 __device__ __forceinline__ void long_reach(const ComponentParams& P, LongLds& S, int b,
-                                           int32_t len, int32_t level, int2* cnt) {
+                                           int32_t len, int32_t level, int32_t* cnt) {
   constexpr int kLanes = kEllWidth / kN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int32_t i = tid / kLanes;
@@ -1112,7 +1110,7 @@ __device__ __forceinline__ void long_reach(const ComponentParams& P, LongLds& S,
   if (all == 0) return;
   const int first = __builtin_ctzll(all);
   int base = 0;
-  if (lane == first) base = lds_add(&cnt->x, total);
+  if (lane == first) base = lds_add(cnt, total);
   base = __builtin_amdgcn_readlane(base, first);
 #pragma unroll
   for (int j = 0; j < kN; ++j) {
@@ -1124,7 +1122,7 @@ __device__ __forceinline__ void long_reach(const ComponentParams& P, LongLds& S,
     S.v[b ^ 1][at] = w[j];
     S.row[b ^ 1][at][0] = make_int4(r[j][0], r[j][1], r[j][2], r[j][3]);
     S.row[b ^ 1][at][1] = make_int4(r[j][4], r[j][5], r[j][6], r[j][7]);
-    if (r[j][0] < 0) cnt->y = 1;
+    if (r[j][0] < 0) atomicOr(cnt, kLongRow);
   }
 }
 
@@ -1133,7 +1131,7 @@ __global__ void __launch_bounds__(kLongThreads) k_long_probe(ComponentParams P) 
   if (ld_relaxed(P.bad_csr) != 0) return;
   const int tid = threadIdx.x;
   for (int32_t i = tid; i < (P.n + 31) / 32; i += kLongThreads) S.bits[i] = 0;
-  if (tid < 3) S.cnt[tid] = make_int2(0, 0);
+  if (tid < 3) S.cnt[tid] = 0;
   __syncthreads();
   if (tid == 0) {
     const int4 lo = P.ell[0];
@@ -1150,9 +1148,9 @@ __global__ void __launch_bounds__(kLongThreads) k_long_probe(ComponentParams P) 
   int32_t len = 1, total = 1, level = 0, near = 0;
   int l3 = 0;
   while (!decline) {
-    int2* cnt = &S.cnt[l3];
+    int32_t* cnt = &S.cnt[l3];
     l3 = l3 == 2 ? 0 : l3 + 1;
-    if (tid == 0) S.cnt[l3] = make_int2(0, 0);
+    if (tid == 0) S.cnt[l3] = 0;
     const int b = level & 1;
     if (len <= kLongThreads / 8)
       long_reach<1>(P, S, b, len, level, cnt);
@@ -1161,12 +1159,11 @@ __global__ void __launch_bounds__(kLongThreads) k_long_probe(ComponentParams P) 
     else
       long_reach<4>(P, S, b, len, level, cnt);
     __syncthreads();
-    const int32_t found = uniform(cnt->x);
+    const int32_t found = uniform(*cnt);
     if (found == 0) break;
     // (a level that grows like a volume's: see component_pass)
     if (level == 3) near = found;
-    decline = uniform(cnt->y) != 0 || found > kLongCap ||
-              (level == 7 && found * 10 >= near * P.growth);
+    decline = found > kLongCap || (level == 7 && found * 10 >= near * P.growth);
     total += found;
     len = found;
     ++level;
