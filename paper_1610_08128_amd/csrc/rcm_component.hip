@@ -406,8 +406,13 @@ struct CsrLevels {
         int h = 0;
         if (sub == 0) h = atomicAdd(&cnt->y, 1);
         h = __shfl(h, 0, kLanes);
+        // (past the list the lanes read the row, unless the level is known
+        // to be too wide: the declined probe of a random graph of 4,000
+        // vertices with rows of 1,570 takes 0.13 ms, 1.06 with all rows read)
         if (h < kHeavyCap) {
           if (sub == 0) S.heavy[h] = i;
+          la = 0;
+        } else if (*static_cast<volatile int32_t*>(&cnt->x) > c.width) {
           la = 0;
         }
       }
@@ -439,7 +444,7 @@ struct CsrLevels {
       rows<kMode, 8, 2>(P, S, c, cur, len, next, cnt);
     __syncthreads();
     const int2 n = make_int2(uniform(cnt->x), uniform(cnt->y));
-    if (n.y == 0) return n.x;
+    if (n.y == 0 || n.x > c.width) return n.x;
     const int32_t nh = n.y < kHeavyCap ? n.y : kHeavyCap;
     for (int32_t h = 0; h < nh; ++h) {
       const int32_t i = S.heavy[h];

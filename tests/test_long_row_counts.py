@@ -127,3 +127,21 @@ def test_only_the_labelled_level_is_wide(children):
     _check(_wide_from_one_side(children, 9000, seed=children))
     _check(I.disjoint_union([I.path(5), g]), reverse_mode=1)
     _check_batch([I.path(9), _wide_from_one_side(children, 100), I.grid2d(9, 7, seed=2)])
+
+
+@pytest.mark.parametrize("leaves", [520, 2047, 2048, 2049, 2500])
+def test_search_levels_of_long_rows(leaves):
+    """Two hundred hubs joined to the same leaves: more rows than the
+    work-group's list of long ones takes, on a level that is known to be too
+    wide, or not, before the last of them is read."""
+    hubs, tail = 200, 9000
+    a = np.arange(hubs) + 1
+    b = np.arange(leaves) + 1 + hubs
+    far = np.arange(tail) + 1 + hubs + leaves
+    u = np.concatenate([np.zeros(hubs, np.int64), np.repeat(a, leaves), [0], far[:-1]])
+    v = np.concatenate([a, np.tile(b, hubs), far])
+    n = int(far[-1]) + 1
+    g = I.from_edges(n, u, v, perm=np.random.default_rng(leaves).permutation(n),
+                     name=f"hubs_{leaves}")
+    _check(g)
+    _check_batch([I.path(9), g], pp_variant=1)
