@@ -254,56 +254,48 @@ __device__ __forceinline__ int32_t ell_near_level(const ELds& L, int32_t b, int3
   return total;
 }
 
-// One level of a search: the vertices ord[fb, fe) claim their neighbours
-// and the vertices they find go to ord[fe + next, ...); returns how many.
-// LPV lanes share a vertex, each taking S of its W columns (a narrow level
-// keeps more lanes busy and each lane's work short); the lanes of a vertex
-// are adjacent, so lane order is the (vertex, column) order.  A vertex is
-// claimed with an LDS atomic minimum of a token (level + 1, lane, slot) and
+// One level of a search wider than ell_near_level takes: the vertices
+// ord[fb, fe), 64 at a time, a lane each, claim their neighbours and the
+// vertices they find go to ord[fe + next, ...); returns how many.  A vertex
+// is claimed with an LDS atomic minimum of a token (level + 1, lane, slot) and
 // is found by the lane that reads its own token back: a vertex of an
 // earlier level keeps its smaller token, an ordered component's kDoneW (0)
 // stays, and of the lanes reaching a new vertex exactly one holds the
-// minimum.  A level wider than one pass of the wave is taken in chunks; a
-// later chunk's tokens are not larger than an earlier chunk's of the same
-// level, so there each lane first reads the words and claims only unclaimed
-// ones.  With kCheck a neighbour in an ordered component sets badm.
-template <int S, int LPV, bool kCheck>
+// minimum.  A later chunk's tokens are not larger than an earlier chunk's of
+// the same level, so each lane first reads the words and claims only
+// unclaimed ones.  With kCheck a neighbour in an ordered component sets badm.
+template <int W, bool kCheck>
 __device__ __forceinline__ int32_t ell_search_level(const ELds& L, int32_t n, int32_t fb,
                                                     int32_t fe, uint32_t lvl,
                                                     unsigned long long& badm) {
-  constexpr int32_t kPer = 64 / LPV;  // vertices per chunk
   const uint32_t lane = threadIdx.x;
   uint32_t* const mine = &L.sink[lane];
   uint16_t* const mine16 = reinterpret_cast<uint16_t*>(mine);
-  const bool one = fe - fb <= kPer;
   int32_t next = 0;
-  for (int32_t q = fb; q < fe; q += kPer) {
-    const int32_t i = q + static_cast<int32_t>(lane) / LPV;
+  for (int32_t q = fb; q < fe; q += 64) {
+    const int32_t i = q + static_cast<int32_t>(lane);
     const bool act = i < fe;
     const uint32_t u = act ? static_cast<uint32_t>(L.ord[i]) : 0u;
-    uint32_t nb[S];
-    load_part<S>(L, u, lane % LPV, nb);
+    uint32_t nb[W];
+    load_row<W>(L, u, nb);
     unsigned nbr = 0;  // (bitwise operators throughout: no branches per slot)
 #pragma unroll
-    for (int j = 0; j < S; ++j) nbr |= static_cast<unsigned>(act & (nb[j] != u)) << j;
-    unsigned cand = nbr;
-    if (!one) {
-      // unclaimed in this search: kFreeW or an earlier search's token, all
-      // of them at least the next larger search field
-      const uint32_t unclaimed = ((lvl >> kPassShift) + 1u) << kPassShift;
-      cand = 0;
+    for (int j = 0; j < W; ++j) nbr |= static_cast<unsigned>(act & (nb[j] != u)) << j;
+    // unclaimed in this search: kFreeW or an earlier search's token, all
+    // of them at least the next larger search field
+    const uint32_t unclaimed = ((lvl >> kPassShift) + 1u) << kPassShift;
+    unsigned cand = 0;
 #pragma unroll
-      for (int j = 0; j < S; ++j)
-        cand |= (nbr >> j & 1u & static_cast<unsigned>(lds_ld(&L.clm[nb[j]]) >= unclaimed)) << j;
-    }
+    for (int j = 0; j < W; ++j)
+      cand |= (nbr >> j & 1u & static_cast<unsigned>(lds_ld(&L.clm[nb[j]]) >= unclaimed)) << j;
 #pragma unroll
-    for (int j = 0; j < S; ++j)
+    for (int j = 0; j < W; ++j)
       atomicMin((cand >> j & 1u) ? &L.clm[nb[j]] : mine,
                 lvl | (lane << 3) | static_cast<uint32_t>(j));
     lds_fence();
     unsigned win = 0;
 #pragma unroll
-    for (int j = 0; j < S; ++j) {
+    for (int j = 0; j < W; ++j) {
       const uint32_t back = lds_ld(&L.clm[nb[j]]);
       win |= (cand >> j & 1u &
               static_cast<unsigned>(back == (lvl | (lane << 3) | static_cast<uint32_t>(j))))
@@ -311,15 +303,14 @@ __device__ __forceinline__ int32_t ell_search_level(const ELds& L, int32_t n, in
       if (kCheck) badm |= __ballot((nbr >> j & 1u) & (back == kDoneW));
     }
     int total;
-    const int pre = ell_wave_prefix(static_cast<uint32_t>(__popc(win)), S >= 4 ? (S == 8 ? 4 : 3)
-                                                                            : (S == 2 ? 2 : 1),
-                                    &total);
+    const int pre =
+        ell_wave_prefix(static_cast<uint32_t>(__popc(win)), W == 8 ? 4 : 3, &total);
     const int32_t base = fe + next + pre;
     // each vertex is found once per pass, so the positions stay below n;
     // clamped to the spare entry all the same (the caller's level-end check
     // reports a count past n)
 #pragma unroll
-    for (int j = 0; j < S; ++j) {
+    for (int j = 0; j < W; ++j) {
       const int32_t at = base + __popc(win & ((1u << j) - 1u));
       *((win >> j & 1u) ? &L.ord[at < n ? at : n] : mine16) = static_cast<uint16_t>(nb[j]);
     }
@@ -361,7 +352,7 @@ __device__ EPass ell_search(const ELds& L, int32_t n, int32_t o, uint32_t root, 
     else if (W == 4 && width <= 128)
       next = ell_near_level<4, 1, 2, false, kCheck>(L, fb, fe, passw, lowest);
     else
-      next = ell_search_level<W, 1, kCheck>(L, n, fb, fe, lvl, badm);
+      next = ell_search_level<W, kCheck>(L, n, fb, fe, lvl, badm);
     next = uniform(next);
     if (next == 0) break;
     fb = fe;
@@ -388,66 +379,49 @@ __device__ EPass ell_search(const ELds& L, int32_t n, int32_t o, uint32_t root, 
 // (0) stays, and the component's first search has checked that none is a
 // neighbour).  The children, already in (degree, id) order along the sorted
 // row, take the parent's first child label plus their rank, the number of
-// children before them in the row.  Lanes as in ell_search_level (LPV lanes
-// per parent, S columns each: lane order is row order).  Returns the number
-// of children placed at ord[e, ...).
-template <int S, int LPV>
+// children before them in the row.  For levels wider than ell_near_level
+// takes: 64 parents at a time, a lane each, so that lane order is row order.
+// Returns the number of children placed at ord[e, ...).
+template <int W>
 __device__ __forceinline__ int32_t ell_label_level(const ELds& L, int32_t n, int32_t b,
                                                    int32_t e) {
-  constexpr int32_t kPer = 64 / LPV;
   const uint32_t lane = threadIdx.x;
   uint32_t* const mine = &L.sink[lane];
   uint16_t* const mine16 = reinterpret_cast<uint16_t*>(mine);
-  // claims of every parent of the level; a one-chunk level keeps its rows
-  // in registers for the count
-  const bool one = e - b <= kPer;
-  uint32_t u1 = 0, nb1[S];
-#pragma unroll
-  for (int j = 0; j < S; ++j) nb1[j] = 0;
-  for (int32_t q = b; q < e; q += kPer) {
-    const int32_t p = q + static_cast<int32_t>(lane) / LPV;
+  // claims of every parent of the level
+  for (int32_t q = b; q < e; q += 64) {
+    const int32_t p = q + static_cast<int32_t>(lane);
     const bool act = p < e;
     const uint32_t u = act ? static_cast<uint32_t>(L.ord[p]) : 0u;
-    uint32_t nb[S];
-    load_part<S>(L, u, lane % LPV, nb);
+    uint32_t nb[W];
+    load_row<W>(L, u, nb);
 #pragma unroll
-    for (int j = 0; j < S; ++j)
+    for (int j = 0; j < W; ++j)
       atomicMin((act & (nb[j] != u)) ? &L.clm[nb[j]] : mine, static_cast<uint32_t>(p) + 1u);
-    if (one) {
-      u1 = u;
-#pragma unroll
-      for (int j = 0; j < S; ++j) nb1[j] = nb[j];
-    }
   }
   lds_fence();
   int32_t placed = 0;
-  for (int32_t q = b; q < e; q += kPer) {
-    const int32_t p = q + static_cast<int32_t>(lane) / LPV;
+  for (int32_t q = b; q < e; q += 64) {
+    const int32_t p = q + static_cast<int32_t>(lane);
     const bool act = p < e;
-    uint32_t u, nb[S];
-    if (one) {
-      u = u1;
-#pragma unroll
-      for (int j = 0; j < S; ++j) nb[j] = nb1[j];
-    } else {
-      u = act ? static_cast<uint32_t>(L.ord[p]) : 0u;
-      load_part<S>(L, u, lane % LPV, nb);
-    }
+    const uint32_t u = act ? static_cast<uint32_t>(L.ord[p]) : 0u;
+    uint32_t nb[W];
+    load_row<W>(L, u, nb);
     unsigned child = 0;
 #pragma unroll
-    for (int j = 0; j < S; ++j) {
+    for (int j = 0; j < W; ++j) {
       const uint32_t c2 = lds_ld(&L.clm[nb[j]]);
       child |= static_cast<unsigned>(act & (nb[j] != u) & (c2 == static_cast<uint32_t>(p) + 1u))
                << j;
     }
     int total;
-    const int pre = ell_wave_prefix(static_cast<uint32_t>(__popc(child)),
-                                    S >= 4 ? (S == 8 ? 4 : 3) : (S == 2 ? 2 : 1), &total);
+    const int pre =
+        ell_wave_prefix(static_cast<uint32_t>(__popc(child)), W == 8 ? 4 : 3, &total);
     const int32_t base = e + placed + pre;
     // (a vertex is placed once per pass: positions below n, clamped to the
     // spare entry all the same)
 #pragma unroll
-    for (int j = 0; j < S; ++j) {
+    for (int j = 0; j < W; ++j) {
       const int32_t at = base + __popc(child & ((1u << j) - 1u));
       *((child >> j & 1u) ? &L.ord[at < n ? at : n] : mine16) = static_cast<uint16_t>(nb[j]);
     }
@@ -481,7 +455,7 @@ __device__ EPass ell_label(const ELds& L, int32_t n, int32_t o, uint32_t root, b
     else if (W == 4 && width <= 128)
       placed = ell_near_level<4, 1, 2, true, false>(L, b, e, 0u, unused);
     else
-      placed = ell_label_level<W, 1>(L, n, b, e);
+      placed = ell_label_level<W>(L, n, b, e);
     placed = uniform(placed);
     if (placed == 0) break;
     if (e + placed > n) {
