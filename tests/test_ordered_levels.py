@@ -81,3 +81,17 @@ def test_list_lengths(width):
     for team in (2, 4):
         _check(g, team_size=team, label_team=team, narrow_cutoff=-1, block_threads=256,
                small_cutoff=1)
+
+
+@pytest.mark.parametrize("team", [128, 256])
+@pytest.mark.parametrize("rebalance", [2, 8])
+def test_keys_run_out(team, rebalance):
+    """2^31 / (2,048 team) levels use up the keys: a strip of about 9,000
+    levels goes back to claims by label for that reason, in the middle of its
+    labelled BFS, and stays there."""
+    g = I.strip_drop(8, 9000, 0.01, seed=team)
+    levels = oracle.rcm(g.n, g.rowptr, g.colidx).stats["num_levels"]
+    # (but for the first few, every level takes keys until they run out)
+    assert levels > (1 << 31) // (team << 11) + 500
+    _check(g, team_size=team, label_team=team, rebalance_levels=rebalance, block_threads=256,
+           narrow_cutoff=-1, small_cutoff=1, relabel_levels=-1)
