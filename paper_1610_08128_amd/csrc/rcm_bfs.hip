@@ -1546,6 +1546,19 @@ __device__ __forceinline__ bool async_bfs_pass(const BfsParams& P, Team& t, Shar
 // Labelled BFS (Algorithm 3).
 // ---------------------------------------------------------------------------
 
+// Whether a vertex's claim word leaves it open to claims by labels from
+// `from` on: unclaimed, or claimed by such a label.  A key (see
+// ordered_label_levels; only with a row copy) is that of a vertex labelled on
+// an earlier level: the levels after those must leave it alone even if only
+// an arc without its way back leads there.
+__device__ __forceinline__ bool open_to(uint32_t claim, uint32_t from) {
+#if defined(RCM_ORDER_CSR) || defined(RCM_ORDER_WIDE)
+  return claim >= from;
+#else
+  return static_cast<int32_t>(claim) >= static_cast<int32_t>(from) || claim == kUnclaimed;
+#endif
+}
+
 // (select2nd, min) SpMSpV contribution of one newly labelled vertex: its
 // label becomes a claim on every neighbour.  Lanes past the row end and
 // already labelled neighbours hold smaller claims, so the min leaves them
@@ -1561,7 +1574,7 @@ __device__ __forceinline__ void claim_batch(const BfsParams& P, const int32_t* n
   for (int j = 0; j < kRB; ++j) cl[j] = ld_relaxed(&P.claim[nb[j]]);
 #pragma unroll
   for (int j = 0; j < kRB; ++j)
-    if (cl[j] > label) atomicMin(&P.claim[nb[j]], label);
+    if (open_to(cl[j], label + 1)) atomicMin(&P.claim[nb[j]], label);
 }
 
 __device__ __forceinline__ void claim_row(const BfsParams& P, int32_t v, int4 info,
@@ -1856,7 +1869,7 @@ __device__ __forceinline__ bool lds_label_levels(const BfsParams& P, Team& t, Sh
 #pragma unroll
         for (int j = 0; j < kRB; ++j) {
           slot[j] = -1;
-          if (nb[j] == e.x || cl[j] < static_cast<uint32_t>(cur_b)) continue;
+          if (nb[j] == e.x || !open_to(cl[j], static_cast<uint32_t>(cur_b))) continue;
           bool fresh = false;
           slot[j] = h_insert(key_ins, nb[j], &fresh);
           if (slot[j] < 0) continue;  // cannot happen: the table is at most half full
@@ -2111,7 +2124,7 @@ __device__ __forceinline__ void global_label_level(const BfsParams& P, Team& t, 
         int32_t* kr = kept_row(S.u, i);
 #pragma unroll
         for (int j = 0; j < kRB; ++j)
-          kr[j] = nb[j] | (cl[j] >= static_cast<uint32_t>(cur_e) && nb[j] != r.x
+          kr[j] = nb[j] | (open_to(cl[j], static_cast<uint32_t>(cur_e)) && nb[j] != r.x
                                ? int32_t(0x80000000u) : 0);
       }
     }
@@ -2313,9 +2326,8 @@ __device__ __forceinline__ void global_label_level(const BfsParams& P, Team& t, 
 // (Graphs with a fixed-stride row copy only: no row is longer than a batch.)
 //
 // Leaves when a list grows too long, the level is narrow or the keys run out:
-// the level's claims are then made again by label, after the words of the
-// vertices that could be mistaken for unlabelled ones (this level's and the
-// one's before) are set below every label.
+// the level's claims are then made again by label.  The keys of the levels
+// before stay, and count as labels from then on (open_to).
 //
 // What is left of a level is memory round trips across the dies: the words
 // read again and the ranks 2.0 us, the claims 2.5, the exchange 2.2.  Measured
@@ -2327,8 +2339,8 @@ __device__ __forceinline__ void global_label_level(const BfsParams& P, Team& t, 
 // 7.5 and 7.5 us (the smallest labels have most of the children, so the
 // lists drift apart quickly).
 __device__ __forceinline__ void ordered_label_levels(const BfsParams& P, Team& t, Shared& S,
-                                                     int32_t first, int32_t end, int32_t& cur_b,
-                                                     int32_t& cur_e, int32_t& levels, bool& done,
+                                                     int32_t end, int32_t& cur_b, int32_t& cur_e,
+                                                     int32_t& levels, bool& done,
                                                      long long& my_m, int& since,
                                                      uint32_t& next_key) {
   const int B = blockDim.x;
@@ -2486,7 +2498,6 @@ __device__ __forceinline__ void ordered_label_levels(const BfsParams& P, Team& t
         }
       }
     }
-    const int32_t last_u = u;
     __syncthreads();
     const long long tb = wall_clock64();
     // Their claims, each by the thread whose parent it is at the next level.
@@ -2556,19 +2567,19 @@ __device__ __forceinline__ void ordered_label_levels(const BfsParams& P, Team& t
     if (widest <= kOrderedCap && total >= P.narrow_cutoff &&
         next_key < 0xFFFFFFFFu - 2 * step)
       continue;
-    // back to claims by label
-    auto below = [&](int32_t v) {
-      __hip_atomic_store(&P.claim[v], static_cast<uint32_t>(first), __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
-    };
-    if (last_u >= 0) below(last_u);
-    for (int32_t k = tid; k < len; k += B) below(list[k].x);
-    team_barrier(t, S, false);
-    if (t.aborted) return;
+    // back to claims by label: in the place of this level's keys, and where
+    // nothing or a larger label is
     for (int32_t k = tid; k < len; k += B) {
       int32_t row[kRB];
       ell_row(P.ell, list[k].x, row);
-      claim_batch(P, row, static_cast<uint32_t>(base + k));
+      const uint32_t label = static_cast<uint32_t>(base + k);
+      uint32_t cl[kRB];
+#pragma unroll
+      for (int j = 0; j < kRB; ++j) cl[j] = ld_relaxed(&P.claim[row[j]]);
+#pragma unroll
+      for (int j = 0; j < kRB; ++j)
+        if (cl[j] >= level_key || open_to(cl[j], label + 1))
+          atomicMin(&P.claim[row[j]], label);
     }
     if (tid == 0) {
       S.lown_base = base;
@@ -2646,7 +2657,7 @@ __device__ __forceinline__ int32_t label_pass(const BfsParams& P, Team& t, Share
     while (!done && (cur_e - cur_b) >= P.narrow_cutoff) {
       if (listed && P.ell != nullptr && since % P.rebalance != 0 &&
           next_key < 0xFFFFFFFFu - 2 * (static_cast<uint32_t>(t.W) << kOrderedBits)) {
-        ordered_label_levels(P, t, S, o, end, cur_b, cur_e, levels, done, my_m, since, next_key);
+        ordered_label_levels(P, t, S, end, cur_b, cur_e, levels, done, my_m, since, next_key);
         listed = false;
       } else {
         global_label_level(P, t, S, end, false, cur_b, cur_e, levels, done, my_m,

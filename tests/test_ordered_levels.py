@@ -95,3 +95,36 @@ def test_keys_run_out(team, rebalance):
     assert levels > (1 << 31) // (team << 11) + 500
     _check(g, team_size=team, label_team=team, rebalance_levels=rebalance, block_threads=256,
            narrow_cutoff=-1, small_cutoff=1, relabel_levels=-1)
+
+
+def _one_way(seed, side, tail, at):
+    """A 3D grid between two paths, and from the second path to the grid's
+    middle an arc without its way back, which every search but one from the
+    second path's end passes too late."""
+    m = side ** 3
+    c = np.arange(m).reshape(side, side, side)
+    a, b = np.arange(tail) + m, np.arange(tail) + m + tail
+    u = [c[:-1].ravel(), c[:, :-1].ravel(), c[:, :, :-1].ravel(), [0], a[:-1], [m - 1], b[:-1]]
+    v = [c[1:].ravel(), c[:, 1:].ravel(), c[:, :, 1:].ravel(), a[:1], a[1:], b[:1], b[1:]]
+    n = m + 2 * tail
+    perm = np.random.default_rng(seed).permutation(n)
+    g = I.from_edges(n, np.concatenate(u), np.concatenate(v), perm=perm)
+    row, col = perm[b[at]], perm[c[side // 2, side // 2, side // 2]]
+    end = g.rowptr[row + 1]
+    rowptr = g.rowptr.copy()
+    rowptr[row + 1:] += 1
+    return I.Graph(n, rowptr, np.insert(g.colidx, end, col).astype(np.int32),
+                   f"one_way_{seed}_{side}_{at}")
+
+
+@pytest.mark.parametrize("seed", range(2, 8))
+@pytest.mark.parametrize("narrow", [-1, 64])
+def test_arcs_back_to_ordered_levels(seed, narrow):
+    """Levels labelled by keys stay as they are when later ones, by labels or
+    by keys, have an arc back to them (it is no error that a traversal of
+    whole components meets)."""
+    for side, at in ((18, 30), (18, 2), (26, 30)):
+        g = _one_way(seed, side, 300, at)
+        for team, rebalance in ((4, 8), (8, 2), (64, 8)):
+            _check(g, team_size=team, label_team=team, block_threads=256, narrow_cutoff=narrow,
+                   rebalance_levels=rebalance, small_cutoff=1, relabel_levels=-1)
