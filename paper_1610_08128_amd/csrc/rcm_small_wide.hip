@@ -72,6 +72,8 @@ struct WShared {
   int32_t bad;
   int32_t root;
   int32_t stop;
+  int32_t named;  // a vertex without neighbours of its own was ordered with a component
+  int32_t run;
   int32_t wsum[kWWaves];
   int32_t wcnt[16 * kWWaves];
   int32_t red[4][kWWaves];
@@ -568,6 +570,7 @@ __global__ void __launch_bounds__(kWT) k_small_wide(SmallJob J, SmallOpts O) {
   bool bad = false;
   if (tid == 0) {
     S.bad = 0;
+    S.named = 0;
     S.edges = 0;
   }
   {
@@ -765,7 +768,8 @@ __global__ void __launch_bounds__(kWT) k_small_wide(SmallJob J, SmallOpts O) {
     }
     // The isolated vertices have the lowest numbers, in the order of their
     // ids: those before s are components of their own, in one go (two level
-    // structures and one level each).
+    // structures and one level each).  Where other rows name one, which only
+    // an asymmetric pattern does, it can have its place already.
     int32_t next = alone;
     for (int32_t hi = isolated; next < hi;) {
       const int32_t mid = (next + hi) >> 1;
@@ -773,20 +777,41 @@ __global__ void __launch_bounds__(kWT) k_small_wide(SmallJob J, SmallOpts O) {
       else hi = mid;
     }
     if (next > alone) {
-      const int32_t run = next - alone;
-      for (int32_t t = tid; t < run; t += kWT) {
-        const int32_t id = L.orig[alone + t];
+      int32_t run = next - alone;
+      auto put = [&](int32_t x, int32_t t) {
+        const int32_t id = L.orig[x];
         const int32_t at = O.reverse_mode ? n - 1 - o - t : o + t;
         J.perm[at] = id + J.id_off;
         if (J.iperm) J.iperm[id] = at + J.pos_off;
-        L.clm[alone + t] = static_cast<uint32_t>(o + t);
+        L.clm[x] = static_cast<uint32_t>(o + t);
+      };
+      if (uniform(S.named) == 0) {
+        for (int32_t t = tid; t < run; t += kWT) put(alone + t, t);
+      } else {
+        // (the first wave, the open ones packed)
+        if (tid < 64) {
+          int32_t t = 0;
+          for (int32_t x0 = alone; x0 < next; x0 += 64) {
+            const int32_t x = x0 + lane;
+            const bool open = x < next && L.clm[x] >= kStamp;
+            const unsigned long long m = __ballot(open);
+            if (open)
+              put(x, t + __builtin_amdgcn_mbcnt_hi(
+                             static_cast<uint32_t>(m >> 32),
+                             __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0)));
+            t += __popcll(m);
+          }
+          if (lane == 0) S.run = t;
+        }
+        __syncthreads();
+        run = uniform(S.run);
       }
       alone = next;
       ncomp += run;
       nbfs_all += 2 * run;
       nlevels += run;
       o += run;
-      since_poll += 64u * static_cast<uint32_t>(run - 1);
+      since_poll += run > 0 ? 64u * static_cast<uint32_t>(run - 1) : 0u;
       __syncthreads();
       if (o >= n) break;
     }
@@ -864,6 +889,7 @@ __global__ void __launch_bounds__(kWT) k_small_wide(SmallJob J, SmallOpts O) {
       J.perm[at] = static_cast<int32_t>(id) + J.id_off;
       if (J.iperm) J.iperm[id] = at + J.pos_off;
       L.clm[x] = static_cast<uint32_t>(O.reverse_mode ? o + t : at);
+      if (static_cast<int32_t>(x) < isolated) S.named = 1;
       const uint32_t rx = L.rec[x];
       edges += static_cast<long long>(nbfs + 1) *
                (((rx >> kBeginBits) & kLenMask) - (rx >> kDiagBit));

@@ -151,3 +151,25 @@ def test_more_vertices_than_the_records_fit(case):
         g = I.from_edges(8191, u, u + 1, diag=False, name="pairs_8191")
     _check(g)
     _check(g, reverse_mode=1, pp_variant=1)
+
+
+@pytest.mark.parametrize("named", [1, 7, 64, 65, 700])
+@pytest.mark.parametrize("apart", [0, 1, 6, 900])
+def test_vertices_that_only_other_rows_name(named, apart):
+    """Leaves of a path's middle whose own rows are empty, between isolated
+    vertices: they belong to the path's component and are ordered once.  (No
+    traversal of whole components meets an error in that.)"""
+    n = 2000
+    i = np.arange(n - 1)
+    hub = np.arange(12)  # a long row
+    total = n + 12 + 2 * apart + named
+    leaves = n + 12 + apart + np.arange(named)
+    u = np.concatenate([i, np.full(12, 20), n // 3 + np.arange(named)])
+    v = np.concatenate([i + 1, n + hub, leaves])
+    g = I.from_edges(total, u, v)
+    rows = np.repeat(np.arange(total), np.diff(g.rowptr))
+    keep = (rows < leaves[0]) | (rows > leaves[-1]) | (rows == g.colidx)
+    g = I.Graph(total, np.concatenate([[0], np.cumsum(np.bincount(rows[keep], minlength=total))])
+                .astype(np.int32), g.colidx[keep], f"named_{named}_{apart}")
+    _check(g)
+    _check(g, pp_variant=1, reverse_mode=1)
