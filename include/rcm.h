@@ -368,7 +368,9 @@ typedef struct {
      the renumbered ids; RCM_WINDOW=0 keeps that engine out), the
      team size, threads per team work-group (with engine 2: 512 for its
      bounded-row variant, whose rows hold at most 8 off-diagonal entries,
-     64 for the general one), labelling sub-team and
+     1,024 for its 16-wave variant, which takes longer rows and graphs too
+     large for the bounded-row one's records, 64 for the general one of the
+     smallest graphs and those that fit no other), labelling sub-team and
      asynchronous round length of a launch with teams (0 if none was called
      for; a single graph in mode 0 shows the settings such a launch would
      take, whether or not its components came to one), and the
