@@ -265,6 +265,9 @@ constexpr int kMiscInts = 28;  // what one readback covers
 // Past the component engine's range: levels from which vertex 0's component is
 // renumbered after its first structure.
 constexpr int32_t kLongLevels = 256;
+// Levels from which a declined probe's way is kept (a sweep over all vertices
+// finds its end: 3 us on 2^19).
+constexpr int32_t kBegunLevels = 32;
 // Declined components of more vertices than this go to teams.
 constexpr int32_t kDeclinedCutoff = 1 << 14;
 
@@ -451,7 +454,9 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
   const bool long_probe = head && opt.component && !component && g.n <= kLongRange &&
                           renumber_from > 0 && window_enabled() && short_rows &&
                           ell != nullptr && ell_enabled();
-  if (head && (component || long_probe) && renumber_from > 0) setup.fill(dkey, 8 * N, 0);
+  // (its distances are kept for a renumbering, or for the team to go on from)
+  const bool keep_way = head && (component || long_probe) && opt.async_search;
+  if (keep_way) setup.fill(dkey, 8 * N, 0);
   HIP_TRY(launch_setup(&setup, s));
   HIP_TRY(launch_validate_scan(g, vinfo, beta, segstats, misc + 0, misc + 3, ell, misc + 6, s));
   ComponentParams C{};
@@ -485,7 +490,7 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
     ComponentParams probe = C;
     probe.bad_csr = misc;
     probe.visit = visit;
-    probe.dkey = renumber_from > 0 ? dkey : nullptr;
+    probe.dkey = keep_way ? dkey : nullptr;
     probe.head = CompTask{0, -1, 0, 0, head_anchor};
     probe.n_head = 1;
     probe.width_limit = short_rows ? kHeadWidth : kComponentCap;
@@ -555,6 +560,11 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
   P.shuffle = opt.shuffle;
   P.relabel_levels = 0;
   P.resume = 0;
+  // A probe that came some way before it declined (a long narrow part into a
+  // wide one) is not walked again.
+  P.start_level = keep_way && h[kCountsAt] != 0 && pr.ecc >= kBegunLevels && pr.ecc < g.n
+                      ? pr.ecc
+                      : 0;
   P.relabelled = 0;
   P.new_of_old = nullptr;
   P.ell = g.nseg == 1 ? ell : nullptr;
@@ -569,7 +579,7 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
     team_ready = true;
     setup.fill(visit, 4 * N, 0);
     setup.fill(claim, 4 * N, -1);
-    if (opt.async_search) setup.fill(P.dkey, 8 * N, 0);
+    if (opt.async_search && P.start_level == 0) setup.fill(P.dkey, 8 * N, 0);
   };
   if (!component && !(probed && long_probe)) {
     ready_team();
@@ -707,12 +717,18 @@ rcm_status run(const Graph& gin, const int32_t* seg_off_host, const Opts& opt, c
       gc[12] = pr.size;
       std::memcpy(&gc[13], &pr.key, sizeof(pr.key));
     } else {
+      if (P.start_level > 0) {
+        ComponentParams begun = C;
+        begun.dkey = dkey;
+        HIP_TRY(launch_front(begun, P.start_level, P.qi, &gctl->front, s));
+      }
       ready_team();
       setup.put(t_big, ht);
       setup.put(results, CompResult{0, 0, 0, 0, 0, 0, 0});
       P.relabel_levels = renumber_from;
       st = launch(t_big, 1, nullptr, 0, 1, true, false);
       P.relabel_levels = 0;
+      P.start_level = 0;
       if (st != RCM_OK) return st;
       HIP_TRY(hipMemcpyAsync(hres, results, sizeof(CompResult), hipMemcpyDeviceToHost, s));
       st = read_ints(gc, &gctl->error, 15, s);

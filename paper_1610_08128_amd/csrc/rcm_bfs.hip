@@ -1314,11 +1314,15 @@ __device__ __forceinline__ bool async_bfs_pass(const BfsParams& P, Team& t, Shar
   const int B = blockDim.x;
   int32_t* tail = t.ctl->tail + parity * 3;
   const int32_t ring = end - o;
+  // (a probe may have begun the first structure of vertex 0's component)
+  const bool begun = find_end && P.start_level > 0;
   if (t.wid == 0 && threadIdx.x == 0) {
-    const int4 ri = P.vinfo[root];
-    __hip_atomic_store(&P.dkey[root], dist_key(tag, 0), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-    st_rec(&P.qi[o], make_int4(root, ri.x, ri.y, 0));
+    if (!begun) {
+      const int4 ri = P.vinfo[root];
+      __hip_atomic_store(&P.dkey[root], dist_key(tag, 0), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+      st_rec(&P.qi[o], make_int4(root, ri.x, ri.y, 0));
+    }
     for (int i = 0; i < 3; ++i) st_relaxed(tail + i, 0);
     st_relaxed(&t.ctl->a_ecc[parity], 0);
     st_relaxed(&t.ctl->a_cnt[parity], 0);
@@ -1329,6 +1333,7 @@ __device__ __forceinline__ bool async_bfs_pass(const BfsParams& P, Team& t, Shar
   team_barrier(t, S, false);
   if (t.aborted) return true;
   int32_t g_b = 0, g_e = 1;  // the frontier: virtual ring indices [g_b, g_e)
+  if (begun) g_e = __builtin_amdgcn_readfirstlane(ld_relaxed(&P.gctl->front));
   int32_t rounds = 0;
   bool overflow = false;
   // diagnostics (work-group 0): steps, records expanded / skipped, ticks

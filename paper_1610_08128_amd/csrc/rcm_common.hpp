@@ -93,7 +93,9 @@ struct alignas(128) GlobalCtl {
   uint32_t p1_tag;
   int32_t p1_size;
   unsigned long long p1_lastkey;
-  int32_t pad[14];
+  // the frontier records a declined probe left (BfsParams::start_level)
+  int32_t front;
+  int32_t pad[13];
 };
 static_assert(sizeof(GlobalCtl) == 128, "one line");
 
@@ -437,6 +439,11 @@ struct BfsParams {
   int32_t resume;
   int32_t relabelled;
   const int32_t* new_of_old;  // null unless relabelled
+  // 0, or how far the component engine's probe came in the first structure of
+  // vertex 0's component before it declined: its distances stand in dkey, and
+  // qi holds GlobalCtl::front records of that distance (launch_front).  The
+  // first asynchronous pass goes on from there.
+  int32_t start_level;
   // Null, or a copy of the rows of a graph whose rows all have at most
   // kEllWidth entries: row v is ell[2v], ell[2v + 1], its entries in order
   // and then v itself.  A neighbour's row is then at an address known from
@@ -548,7 +555,7 @@ constexpr int32_t kComponentRange = 1 << 19;
 constexpr uint32_t kProbeTag = (1u << 6) | 1u;  // component 0, pass 1
 // The first level structure of vertex 0's component.
 struct ComponentProbe {
-  int32_t ecc;
+  int32_t ecc;                 // (declined: the last level expanded completely)
   int32_t size;
   unsigned long long key;      // minimum (degree, id) of its last level
 };
@@ -593,6 +600,11 @@ hipError_t launch_component(const ComponentParams& p, hipStream_t s);
 // counts[0] is raised when its levels are wider than a long component's.
 constexpr int32_t kLongRange = 1146880;
 hipError_t launch_long_probe(const ComponentParams& p, hipStream_t s);
+// What a probe that declined behind `level` leaves to the team: the records of
+// that level in qi, counted in *front (0 before), and the words of those
+// behind it unvisited again.
+hipError_t launch_front(const ComponentParams& p, int32_t level, int4* qi, int32_t* front,
+                        hipStream_t s);
 // The declined tasks, in list order: the head and the large ones, the small
 // ones.
 hipError_t launch_declined(const ComponentParams& p, CompTask* big_out, CompTask* small_out,

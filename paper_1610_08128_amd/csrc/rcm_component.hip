@@ -964,7 +964,10 @@ __device__ __forceinline__ void order_component(const ComponentParams& P, Lds& S
       ell = false;
       continue;
     }
-    if (c.state != kRun) return;
+    if (c.state != kRun) {
+      if (kind == kProbe && threadIdx.x == 0) P.probe->ecc = c.level;
+      return;
+    }
     if (kind == kProbe) {
       if (threadIdx.x == 0) {
         P.probe->ecc = r.ecc;
@@ -1183,7 +1186,10 @@ __global__ void __launch_bounds__(kLongThreads) k_long_probe(ComponentParams P) 
     }
   }
   if (decline) {
-    if (tid == 0) atomicAdd(&P.counts[0], 1);
+    if (tid == 0) {
+      P.probe->ecc = level > 0 ? level - 1 : 0;
+      atomicAdd(&P.counts[0], 1);
+    }
     return;
   }
   // the minimum (degree, id) of the last level
@@ -1227,6 +1233,23 @@ k_declined(ComponentParams P, CompTask* __restrict__ big_out, CompTask* __restri
   }
 }
 
+// A declined probe's last level that was expanded completely: its vertices'
+// records; what lies behind them is found again.
+__global__ void __launch_bounds__(256)
+k_front(ComponentParams P, int32_t level, int4* __restrict__ qi, int32_t* __restrict__ front) {
+  const unsigned long long at = distance_word(level);
+  for (int32_t v = blockIdx.x * 256 + threadIdx.x; v < P.n; v += gridDim.x * 256) {
+    const unsigned long long w = P.dkey[v];
+    if (w == 0 || w > at) continue;  // (a larger word is a shorter distance)
+    if (w == at) {
+      const int4 inf = P.vinfo[v];
+      qi[atomicAdd(front, 1)] = make_int4(v, inf.x, inf.y, level);
+    } else {
+      P.dkey[v] = 0;
+    }
+  }
+}
+
 }  // namespace
 
 hipError_t launch_component(const ComponentParams& p, hipStream_t s) {
@@ -1240,6 +1263,12 @@ hipError_t launch_component(const ComponentParams& p, hipStream_t s) {
 
 hipError_t launch_long_probe(const ComponentParams& p, hipStream_t s) {
   k_long_probe<<<1, kLongThreads, 0, s>>>(p);
+  return hipGetLastError();
+}
+
+hipError_t launch_front(const ComponentParams& p, int32_t level, int4* qi, int32_t* front,
+                        hipStream_t s) {
+  k_front<<<static_cast<unsigned>((p.n + 1023) / 1024), 256, 0, s>>>(p, level, qi, front);
   return hipGetLastError();
 }
 
