@@ -271,6 +271,9 @@ __device__ __forceinline__ int32_t ell_search_level(const ELds& L, int32_t n, in
   const uint32_t lane = threadIdx.x;
   uint32_t* const mine = &L.sink[lane];
   uint16_t* const mine16 = reinterpret_cast<uint16_t*>(mine);
+  // (always so for levels this wide; taken for granted, the kernel needs three
+  // registers more and the 64 x 64 grid takes 159.5 us instead of 157.9)
+  const bool chunks = fe - fb > 64;
   int32_t next = 0;
   for (int32_t q = fb; q < fe; q += 64) {
     const int32_t i = q + static_cast<int32_t>(lane);
@@ -281,13 +284,16 @@ __device__ __forceinline__ int32_t ell_search_level(const ELds& L, int32_t n, in
     unsigned nbr = 0;  // (bitwise operators throughout: no branches per slot)
 #pragma unroll
     for (int j = 0; j < W; ++j) nbr |= static_cast<unsigned>(act & (nb[j] != u)) << j;
-    // unclaimed in this search: kFreeW or an earlier search's token, all
-    // of them at least the next larger search field
-    const uint32_t unclaimed = ((lvl >> kPassShift) + 1u) << kPassShift;
-    unsigned cand = 0;
+    unsigned cand = nbr;
+    if (chunks) {
+      // unclaimed in this search: kFreeW or an earlier search's token, all
+      // of them at least the next larger search field
+      const uint32_t unclaimed = ((lvl >> kPassShift) + 1u) << kPassShift;
+      cand = 0;
 #pragma unroll
-    for (int j = 0; j < W; ++j)
-      cand |= (nbr >> j & 1u & static_cast<unsigned>(lds_ld(&L.clm[nb[j]]) >= unclaimed)) << j;
+      for (int j = 0; j < W; ++j)
+        cand |= (nbr >> j & 1u & static_cast<unsigned>(lds_ld(&L.clm[nb[j]]) >= unclaimed)) << j;
+    }
 #pragma unroll
     for (int j = 0; j < W; ++j)
       atomicMin((cand >> j & 1u) ? &L.clm[nb[j]] : mine,
