@@ -8,7 +8,8 @@
 // work-group of its own (a bitonic sort of (column, position) pairs, in LDS
 // or, for very long rows, in a scratch array).
 // Product: a group of eight lanes per row (rows of meshes hold 5 to 13
-// entries), each lane striding the row, then a reduction across the group.
+// entries), each lane striding the row, then a reduction across the group;
+// the rest of a long row by the whole wave.
 
 #include "rcm_apply.h"
 
@@ -314,97 +315,219 @@ k_sort_long_rows(int32_t n, const int32_t* __restrict__ colidx, const double* __
   }
 }
 
-// One batch of eight entries of each of the group's rows: entry `off` + lane,
-// rows [first, end).  Branch-free, so that every load is issued before the
-// first is waited for: past its end a row's last entry is read again (no row
-// is empty) and not added.  (Unsigned: the last rows of a matrix of nearly
-// 2^31 entries reach past that.)
-template <bool kVals>
-__device__ __forceinline__ void load_batch(const int32_t* __restrict__ colidx,
-                                           const double* __restrict__ vals, const uint32_t* at,
-                                           const uint32_t* end, uint32_t off, int32_t* c,
-                                           double* w) {
+// One batch of the product: eight entries, from `off` on, of each of a group's
+// kRows rows, whose entries left are [at, end) with `at` the lane's first one.
+// (Unsigned throughout: the last rows of nearly 2^31 entries reach past that.)
+//
+// Near rows, none of them empty and all of at most two batches: branch-free,
+// so that every load is issued before the first is waited for; past its end a
+// row's last entry is read again, and not added.
+template <bool kVals, int kRows>
+__device__ __forceinline__ void near_load(const int32_t* __restrict__ colidx,
+                                          const double* __restrict__ vals, const uint32_t* at,
+                                          const uint32_t* end, uint32_t off, int32_t* c,
+                                          double* w) {
 #pragma unroll
-  for (int u = 0; u < kUnroll; ++u) {
+  for (int u = 0; u < kRows; ++u) {
     const uint32_t e = min(at[u] + off, end[u] - 1u);
     c[u] = colidx[e];
     w[u] = kVals ? vals[e] : 1.0;
   }
 }
-__device__ __forceinline__ void add_batch(const double* __restrict__ x, const uint32_t* at,
-                                          const uint32_t* end, uint32_t off, const int32_t* c,
-                                          const double* w, double* s) {
-  double g[kUnroll];
+template <int kRows>
+__device__ __forceinline__ void near_add(const double* __restrict__ x, const uint32_t* at,
+                                         const uint32_t* end, uint32_t off, const int32_t* c,
+                                         const double* w, double* s) {
+  double g[kRows];
 #pragma unroll
-  for (int u = 0; u < kUnroll; ++u) g[u] = x[c[u]];
+  for (int u = 0; u < kRows; ++u) g[u] = x[c[u]];
 #pragma unroll
-  for (int u = 0; u < kUnroll; ++u) {
+  for (int u = 0; u < kRows; ++u) {
     const double t = fma(w[u], g[u], s[u]);
     s[u] = at[u] + off < end[u] ? t : s[u];
   }
 }
 
-// y = A x.  Bound by the matrix's bytes, so each group keeps kUnroll rows in
-// flight: the row bounds of all of them, then eight entries of each, then the
-// next eight with the first ones' gathers of x, and so on.  A die takes consecutive rows
-// (xcd_tile).  The sums are those of one row at a time: a lane's entries in
-// order by fma, then halves of the group.  A wave with an empty row, or one
-// of more than kMediumRow entries, takes its rows one after another.  On the
-// 128^3 grid in banded order with values: 76 us with one row in flight,
-// 51 us so (4.2 TB/s of 217 MB; a copy reaches 5.05).
-template <bool kVals>
+// Other rows: through buffers over the wave's entries and over x, where a lane
+// without an entry asks for a place past the end, which makes no request and
+// gives 0.  Read again and again, the last entries of the shorter rows of a
+// wave cost as many requests as the entries themselves (a random geometric
+// graph of 1,000,000 vertices, rows of up to 30 entries, in random order with
+// values: 172 us, 146 so).
+constexpr uint32_t kNowhere = 0xFFFFFFF8u;
+constexpr uint32_t kFarSpan = 1u << 28;  // entries a wave's buffers cover
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, static_cast<int>(bytes),
+                                           0x00020000);  // 32-bit raw data
+}
+__device__ __forceinline__ double load_f64(__amdgpu_buffer_rsrc_t b, uint32_t byte) {
+  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(b, byte, 0, 0));
+}
+template <bool kVals, int kRows>
+__device__ __forceinline__ void far_load(__amdgpu_buffer_rsrc_t colidx,
+                                         __amdgpu_buffer_rsrc_t vals, const uint32_t* at,
+                                         const uint32_t* end, uint32_t off, int32_t* c,
+                                         double* w) {
+#pragma unroll
+  for (int u = 0; u < kRows; ++u) {
+    const uint32_t e = at[u] + off;
+    const bool has = e < end[u];
+    c[u] = __builtin_amdgcn_raw_buffer_load_b32(colidx, has ? 4u * e : kNowhere, 0, 0);
+    w[u] = kVals ? load_f64(vals, has ? 8u * e : kNowhere) : 1.0;
+  }
+}
+template <int kRows>
+__device__ __forceinline__ void far_add(__amdgpu_buffer_rsrc_t x, const uint32_t* at,
+                                        const uint32_t* end, uint32_t off, const int32_t* c,
+                                        const double* w, double* s) {
+  double g[kRows];
+#pragma unroll
+  for (int u = 0; u < kRows; ++u)
+    g[u] = load_f64(x, at[u] + off < end[u] ? 8u * static_cast<uint32_t>(c[u]) : kNowhere);
+#pragma unroll
+  for (int u = 0; u < kRows; ++u) {
+    const double t = fma(w[u], g[u], s[u]);
+    s[u] = at[u] + off < end[u] ? t : s[u];
+  }
+}
+
+// y = A x.  Bound by the matrix's bytes where x's gathers hit the die's L2, by
+// those gathers else, so each group of eight lanes keeps kRows rows in flight:
+// the bounds of all of them, then eight entries of each, then the next eight
+// with the first ones' gathers of x, and so on.  A die takes consecutive rows
+// (xcd_tile).  Up to kMediumRow entries the sums are those of one row at a
+// time: a lane's entries in order by fma, then halves of the group.  Past
+// that the batches go on while half of a wave's rows have entries left; what
+// is left of a row is then added by its lanes (up to 64 entries) or by the
+// whole wave.
+// On the 128^3 grid in banded order with values: 76 us with one row in
+// flight, 51 us with four (4.2 TB/s of 217 MB; a copy reaches 5.05).  10,000
+// rows of 1,000 entries with values: 62 us as a lane group a row with one in
+// flight, 202 us with four, 58 us so.
+template <bool kVals, int kRows>
 __global__ void __launch_bounds__(kThreads)
 k_spmv(int32_t n, const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
        const double* __restrict__ vals, const double* __restrict__ x, double* __restrict__ y) {
-  const int64_t r0 = xcd_tile() * kTileRows + threadIdx.x / kGroup;
+  const int64_t r0 = xcd_tile() * (kGroups * kRows) + threadIdx.x / kGroup;
   const uint32_t lane = threadIdx.x % kGroup;
-  uint32_t at[kUnroll], end[kUnroll];
-  double s[kUnroll];
-  int32_t longest = 0, shortest = 1;
+  uint32_t at[kRows], end[kRows];
+  double s[kRows];
 #pragma unroll
-  for (int u = 0; u < kUnroll; ++u) {
+  for (int u = 0; u < kRows; ++u) {
     const int64_t r = r0 + u * kGroups;
     const int32_t rr = r < n ? static_cast<int32_t>(r) : n - 1;
     at[u] = static_cast<uint32_t>(rowptr[rr]);
     end[u] = static_cast<uint32_t>(rowptr[rr + 1]);
   }
+  // entries counted from the wave's first one
+  const uint32_t first = __builtin_amdgcn_readfirstlane(at[0]);
+  const uint32_t span = __builtin_amdgcn_readlane(end[kRows - 1], 63) - first;
+  colidx += first;
+  if (kVals) vals += first;
+  uint32_t longest = 0, shortest = 1;
 #pragma unroll
-  for (int u = 0; u < kUnroll; ++u) {
-    const int32_t len = static_cast<int32_t>(end[u] - at[u]);
-    longest = max(longest, len);
-    shortest = min(shortest, len);
-    at[u] += lane;
+  for (int u = 0; u < kRows; ++u) {
+    longest = max(longest, end[u] - at[u]);
+    shortest = min(shortest, end[u] - at[u]);
+    at[u] += lane - first;
+    end[u] -= first;
     s[u] = 0.0;
   }
-  if (__all(shortest > 0 && longest <= kMediumRow)) {
-    int32_t c[kUnroll], c2[kUnroll];
-    double w[kUnroll], w2[kUnroll];
-    load_batch<kVals>(colidx, vals, at, end, 0, c, w);
-    for (int32_t off = 0;;) {
-      const bool more = __any(off + kGroup < longest);
-      if (more) load_batch<kVals>(colidx, vals, at, end, off + kGroup, c2, w2);
-      add_batch(x, at, end, off, c, w, s);
-      if (!more) break;
-      off += kGroup;
-      const bool more2 = __any(off + kGroup < longest);
-      if (more2) load_batch<kVals>(colidx, vals, at, end, off + kGroup, c, w);
-      add_batch(x, at, end, off, c2, w2, s);
-      if (!more2) break;
-      off += kGroup;
-    }
-  } else {
+  uint32_t off = 0;  // entries of every row that are done
+  int32_t c[kRows], c2[kRows];
+  double w[kRows], w2[kRows];
+  if (__all(shortest > 0 && longest <= 2 * kGroup)) {
+    near_load<kVals, kRows>(colidx, vals, at, end, 0, c, w);
+    const bool more = __any(longest > kGroup);
+    if (more) near_load<kVals, kRows>(colidx, vals, at, end, kGroup, c2, w2);
+    near_add<kRows>(x, at, end, 0, c, w, s);
+    if (more) near_add<kRows>(x, at, end, kGroup, c2, w2, s);
+    off = 2 * kGroup;
+  } else if (span < kFarSpan && n < 1 << 29) {  // (32-bit byte offsets)
+    const __amdgpu_buffer_rsrc_t bc = buffer_of(colidx, 4u * span);
+    const __amdgpu_buffer_rsrc_t bv = buffer_of(vals, 8u * span);
+    const __amdgpu_buffer_rsrc_t bx = buffer_of(x, 8u * static_cast<uint32_t>(n));
+    auto worth = [&](uint32_t o) -> bool {
+      if (o < kMediumRow) return __any(o < longest);
+      if (kRows == 1) return false;
+      int rows = 0;
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
-      for (uint32_t e = at[u]; e < end[u]; e += kGroup)
-        s[u] = fma(kVals ? vals[e] : 1.0, x[colidx[e]], s[u]);
+      for (int u = 0; u < kRows; ++u) rows += __popcll(__ballot(at[u] - lane + o < end[u]));
+      return rows >= 32 * kRows;
+    };
+    far_load<kVals, kRows>(bc, bv, at, end, 0, c, w);
+    while (true) {
+      const bool more = worth(off + kGroup);
+      if (more) far_load<kVals, kRows>(bc, bv, at, end, off + kGroup, c2, w2);
+      far_add<kRows>(bx, at, end, off, c, w, s);
+      off += kGroup;
+      if (!more) break;
+      const bool more2 = worth(off + kGroup);
+      if (more2) far_load<kVals, kRows>(bc, bv, at, end, off + kGroup, c, w);
+      far_add<kRows>(bx, at, end, off, c2, w2, s);
+      off += kGroup;
+      if (!more2) break;
+    }
+  }
+  if (__any(off < longest)) {
+    const uint32_t wave_lane = threadIdx.x & 63;
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) {
+      const uint32_t b = at[u] - lane + off;
+      const uint32_t left = b < end[u] ? end[u] - b : 0u;
+      if (left <= 64)
+        for (uint32_t e = b + lane; e < end[u]; e += kGroup)
+          s[u] = fma(kVals ? vals[e] : 1.0, x[colidx[e]], s[u]);
+      unsigned long long rows = __ballot(lane == 0 && left > 64);
+      while (rows != 0) {
+        const int from = __builtin_ctzll(rows);
+        rows &= rows - 1;
+        uint32_t e = __builtin_amdgcn_readlane(b, from) + wave_lane;
+        const uint32_t to = __builtin_amdgcn_readlane(end[u], from);
+        double p = 0.0, q = 0.0;
+        for (; e + 64 < to; e += 128) {
+          const int32_t c0 = colidx[e], c1 = colidx[e + 64];
+          const double w0 = kVals ? vals[e] : 1.0, w1 = kVals ? vals[e + 64] : 1.0;
+          p = fma(w0, x[c0], p);
+          q = fma(w1, x[c1], q);
+        }
+        if (e < to) p = fma(kVals ? vals[e] : 1.0, x[colidx[e]], p);
+        p += q;
+#pragma unroll
+        for (int m = kGroup; m < 64; m <<= 1) p += __shfl_xor(p, m, 64);
+        if (wave_lane / kGroup == static_cast<uint32_t>(from) / kGroup) s[u] += p;
+      }
+    }
   }
 #pragma unroll
-  for (int u = 0; u < kUnroll; ++u) {
+  for (int u = 0; u < kRows; ++u) {
 #pragma unroll
-    for (int off = kGroup / 2; off > 0; off >>= 1) s[u] += __shfl_xor(s[u], off, kGroup);
+    for (int m = kGroup / 2; m > 0; m >>= 1) s[u] += __shfl_xor(s[u], m, kGroup);
     const int64_t r = r0 + u * kGroups;
     if (lane == 0 && r < n) y[r] = s[u];
   }
+}
+
+// Rows in flight per group: as many as leave the chip full.  With values, and
+// 1, 2 and 4 in flight: 200,000 rows of 1 to 30 entries in random order 16.3,
+// 17.4, 18.9 us; 450,000 rows, one in twenty of 150 entries and the others of
+// 6, 60.5, 49.4, 59.2; the banded 128^3 grid 54, 39, 38.
+template <bool kVals, int kRows>
+void launch_spmv(int32_t n, const int32_t* rowptr, const int32_t* colidx, const double* vals,
+                 const double* x, double* y, hipStream_t s) {
+  constexpr int kTile = kGroups * kRows;
+  k_spmv<kVals, kRows><<<xcd_grid((static_cast<int64_t>(n) + kTile - 1) / kTile), kThreads, 0,
+                         s>>>(n, rowptr, colidx, vals, x, y);
+}
+template <bool kVals>
+void launch_spmv(int32_t n, const int32_t* rowptr, const int32_t* colidx, const double* vals,
+                 const double* x, double* y, hipStream_t s) {
+  if (n < 1 << 18)
+    launch_spmv<kVals, 1>(n, rowptr, colidx, vals, x, y, s);
+  else if (n < 1 << 19)
+    launch_spmv<kVals, 2>(n, rowptr, colidx, vals, x, y, s);
+  else
+    launch_spmv<kVals, 4>(n, rowptr, colidx, vals, x, y, s);
 }
 
 // The rows' kernels of rcm_permute.
@@ -489,11 +612,10 @@ rcm_status rcm_spmv(int32_t n, const int32_t* rowptr, const int32_t* colidx, con
   if (n == 0) return RCM_OK;
   if (!rowptr || !x || !y) return RCM_ERR_INVALID_ARGUMENT;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const unsigned blocks = xcd_grid((static_cast<int64_t>(n) + kTileRows - 1) / kTileRows);
   if (vals)
-    k_spmv<true><<<blocks, kThreads, 0, s>>>(n, rowptr, colidx, vals, x, y);
+    launch_spmv<true>(n, rowptr, colidx, vals, x, y, s);
   else
-    k_spmv<false><<<blocks, kThreads, 0, s>>>(n, rowptr, colidx, vals, x, y);
+    launch_spmv<false>(n, rowptr, colidx, vals, x, y, s);
   return hipGetLastError() == hipSuccess ? RCM_OK : RCM_ERR_HIP;
 }
 

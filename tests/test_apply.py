@@ -297,3 +297,93 @@ def test_gpu_permute_few_entries(entries, values):
     assert np.array_equal(bci.cpu().numpy(), want_ci)
     assert not values or np.array_equal(bv.cpu().numpy(), want_v)
     assert bool((buf[size:] == 0x5A).all())
+
+
+def _blocks_of_rows(n, seed):
+    """Rows in stretches of 300 of a kind, so that waves meet each alone and
+    next to others: none, few and two batches of entries, rows at the lengths
+    at which a wave goes on by other means, a few long ones among short."""
+    rng = np.random.default_rng(seed)
+    kinds = [(5,), (16,), (17,), (0,), (0, 3), (1, 30), (64,), (65,), (100,), (6, 6, 6, 150),
+             (6,) * 40 + (3000,), (72, 128, 129), (8, 9), (20, 0, 500), (192, 193, 0), (63, 64)]
+    lengths = np.concatenate([rng.choice(kinds[i % len(kinds)] if i < 40 else (0, 1, 2, 5, 7), 300)
+                              for i in range(n // 300 + 1)])[:n]
+    rowptr = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+    return rowptr, rng.integers(0, n, int(rowptr[-1])).astype(np.int32)
+
+
+# the product's numbers of rows in flight change at 2^18 and 2^19 rows
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [5000, 2**18 - 1, 2**18, 2**19 - 1, 2**19, 2**19 + 333])
+@pytest.mark.parametrize("values", [True, False])
+def test_gpu_spmv_kinds_of_rows(n, values):
+    """Each |y_i - y'_i| <= 2 * L_i * u * sum_j |a_ij x_j| (two summation orders,
+    each within L_i * u of the exact sum); u = 2^-53."""
+    import torch
+    from paper_1610_08128_amd import apply
+
+    rowptr, colidx = _blocks_of_rows(n, n)
+    rng = np.random.default_rng(n + 1)
+    x = rng.standard_normal(n)
+    vals = rng.standard_normal(colidx.size) if values else np.ones(colidx.size)
+    y = apply.spmv(torch.from_numpy(rowptr).cuda(), torch.from_numpy(colidx).cuda(),
+                   torch.from_numpy(x).cuda(),
+                   torch.from_numpy(vals).cuda() if values else None).cpu().numpy()
+    A = sp.csr_matrix((vals, colidx, rowptr), shape=(n, n))
+    absum = sp.csr_matrix((np.abs(vals), colidx, rowptr), shape=(n, n)) @ np.abs(x)
+    L = np.diff(rowptr).astype(np.float64)
+    assert np.all(np.abs(y - A @ x) <= 2 * L * 2.0**-53 * absum)
+
+
+@pytest.mark.gpu
+def test_gpu_spmv_special_values():
+    """Infinities and NaN reach the rows that hold them and no other."""
+    import torch
+    from paper_1610_08128_amd import apply
+
+    n = 5000
+    rowptr, colidx = _blocks_of_rows(n, 3)
+    rng = np.random.default_rng(4)
+    x = rng.standard_normal(n)
+    vals = rng.standard_normal(colidx.size)
+    at = rng.integers(0, colidx.size, 40)
+    vals[at] = np.where(np.arange(40) % 2, np.nan, np.inf)
+    x[rng.integers(0, n, 5)] = np.nan
+    bad = ~np.isfinite(vals) | ~np.isfinite(x[colidx])
+    rows = np.repeat(np.arange(n), np.diff(rowptr))
+    want = np.zeros(n, bool)
+    want[rows[bad]] = True
+    y = apply.spmv(torch.from_numpy(rowptr).cuda(), torch.from_numpy(colidx).cuda(),
+                   torch.from_numpy(x).cuda(), torch.from_numpy(vals).cuda()).cpu().numpy()
+    assert np.array_equal(~np.isfinite(y), want)
+
+
+@pytest.mark.gpu
+def test_gpu_spmv_past_the_buffers():
+    """A row of more entries than a wave's 32-bit offsets cover, among short
+    ones, and a vector of 2^29 entries and more.  Whole numbers, so that every
+    sum is exact."""
+    import torch
+    from paper_1610_08128_amd import apply
+
+    long = (1 << 28) + 77
+    rowptr = torch.tensor([0, 20, 20 + long, 50 + long], dtype=torch.int32, device="cuda")
+    colidx = torch.zeros(50 + long, dtype=torch.int32, device="cuda")
+    colidx[:20] = 1
+    colidx[-30:] = 2
+    colidx[100:1100] = 2
+    print(f"row of {long}", flush=True)
+    y = apply.spmv(rowptr, colidx, torch.tensor([1.0, 3.0, 5.0], dtype=torch.float64,
+                                                device="cuda"))
+    assert y.tolist() == [60.0, long + 4000.0, 150.0]
+    del colidx
+    n = (1 << 29) + 3
+    print(f"vector of {n}", flush=True)
+    rowptr = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    rowptr[n - 4:] = torch.tensor([0, 20, 40, 140, 141], dtype=torch.int32, device="cuda")
+    colidx = torch.arange(n - 141, n, dtype=torch.int32, device="cuda")
+    x = torch.zeros(n, dtype=torch.float64, device="cuda")
+    x[-141:] = torch.arange(141, dtype=torch.float64, device="cuda")
+    y = apply.spmv(rowptr, colidx, x)
+    assert y[-4:].tolist() == [190.0, 590.0, float(sum(range(40, 140))), 140.0]
+    assert not bool(y[:-4].any())
