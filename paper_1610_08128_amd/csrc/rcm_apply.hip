@@ -61,20 +61,6 @@ ApplyLayout apply_layout(int32_t n, int64_t nnz, bool with_values) {
   return L;
 }
 
-// Work-groups are dealt round-robin to the chip's kXcds dies, each with an L2
-// of its own.  This numbering gives a die consecutive tiles: block b of a
-// grid of kXcds * per blocks takes tile (b mod kXcds) * per + b / kXcds.  Rows
-// of a banded matrix that are near each other then gather the same lines of
-// x or iperm through one L2 instead of eight.
-constexpr int kXcds = 8;
-__device__ __forceinline__ int64_t xcd_tile() {
-  const int64_t per = gridDim.x / kXcds;
-  return static_cast<int64_t>(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
-}
-inline unsigned xcd_grid(int64_t tiles) {
-  return static_cast<unsigned>((tiles + kXcds - 1) / kXcds * kXcds);
-}
-
 // Row k of B starts at begin[k] in A (begin null: not kept) and has deg[k]
 // entries; counts (null without any entry) starts at 0.
 __global__ void k_new_degrees(int32_t n, const int32_t* __restrict__ rowptr,

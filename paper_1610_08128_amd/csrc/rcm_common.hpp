@@ -210,6 +210,86 @@ __device__ __forceinline__ int wave_incl_scan(int x) {
   return x;
 }
 
+// A value that is the same in every lane, as a scalar: branches on it are
+// scalar branches, and what it is added up to takes no vector register.
+__device__ __forceinline__ int32_t uniform(int32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ uint64_t uniform(uint64_t x) {
+  return (static_cast<uint64_t>(static_cast<uint32_t>(uniform(static_cast<int32_t>(x >> 32)))) << 32) |
+         static_cast<uint32_t>(uniform(static_cast<int32_t>(x)));
+}
+
+// Inclusive prefix sum within a wave by DPP row shifts and broadcasts: six
+// dependent vector instructions, where a shuffle scan makes six trips
+// through the LDS pipe.
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return x;
+}
+
+// A value of the lane that a DPP control names.
+template <int kCtrl>
+__device__ __forceinline__ uint32_t dpp(uint32_t x) {
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
+      static_cast<int>(x), static_cast<int>(x), kCtrl, 0xf, 0xf, false));
+}
+// Minimum over the 16 lanes of a DPP row, in every lane of it.
+__device__ __forceinline__ uint32_t row_min(uint32_t x) {
+  uint32_t y = dpp<0xB1>(x);   // quad_perm: lane ^ 1
+  x = y < x ? y : x;
+  y = dpp<0x4E>(x);            // quad_perm: lane ^ 2
+  x = y < x ? y : x;
+  y = dpp<0x141>(x);           // row_half_mirror
+  x = y < x ? y : x;
+  y = dpp<0x140>(x);           // row_mirror
+  return y < x ? y : x;
+}
+
+// Equal pairs among the entries of a matrix row: x0 holds entries 0 .. 15 in
+// the 16 lanes, x1 entries 16 .. 31 (lanes past the row's end hold distinct
+// fillers); each pair is compared by rotating one side.
+template <int kStep>
+__device__ __forceinline__ uint32_t same_in(uint32_t x) {
+  if constexpr (kStep > 8) return 0u;
+  else return (x == dpp<0x120 + kStep>(x) ? 1u : 0u) | same_in<kStep + 1>(x);
+}
+template <int kStep>
+__device__ __forceinline__ uint32_t same_between(uint32_t x, uint32_t y) {
+  if constexpr (kStep > 15) return 0u;
+  else return (x == dpp<0x120 + kStep>(y) ? 1u : 0u) | same_between<kStep + 1>(x, y);
+}
+
+// x added to *p by one lane (the compiler would wrap a plain atomic of one
+// lane in a second reduction over the wave, 2 % of the 223 x 227 grid's time).
+__device__ __forceinline__ int32_t lds_add(int32_t* p, int32_t x) {
+  const uint32_t at = static_cast<uint32_t>(
+      reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) int32_t*)p));
+  int32_t old;
+  asm volatile("ds_add_rtn_u32 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(old)
+               : "v"(at), "v"(x)
+               : "memory");
+  return old;
+}
+
+// Work-groups are dealt round-robin to the chip's kXcds dies, each with an L2
+// of its own.  This numbering gives a die consecutive tiles: block b of a
+// grid of kXcds * per blocks takes tile (b mod kXcds) * per + b / kXcds.  Rows
+// of a banded matrix that are near each other then gather the same lines
+// through one L2 instead of eight.
+constexpr int kXcds = 8;
+__device__ __forceinline__ int64_t xcd_tile() {
+  const int64_t per = gridDim.x / kXcds;
+  return static_cast<int64_t>(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
+}
+inline unsigned xcd_grid(int64_t tiles) {
+  return static_cast<unsigned>((tiles + kXcds - 1) / kXcds * kXcds);
+}
+
 // Exclusive block scan of one int per thread; returns the exclusive prefix and
 // the block total through *total.  scratch: >= 17 ints of LDS.  All threads
 // of the block must call it.

@@ -139,27 +139,6 @@ struct Pass {
   long long m;      // their degrees (labelled passes)
 };
 
-// Inclusive prefix sum within a wave by DPP row shifts and broadcasts: six
-// dependent vector instructions, where a shuffle scan makes six trips
-// through the LDS pipe.
-__device__ __forceinline__ int wave_scan(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
-  return x;
-}
-
-// A value that is the same in every lane, as a scalar: branches on it are
-// scalar branches, and what it is added up to takes no vector register.
-__device__ __forceinline__ int32_t uniform(int32_t x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ uint64_t uniform(uint64_t x) {
-  return (static_cast<uint64_t>(static_cast<uint32_t>(uniform(static_cast<int32_t>(x >> 32)))) << 32) |
-         static_cast<uint32_t>(uniform(static_cast<int32_t>(x)));
-}
-
 __device__ __forceinline__ void flag_error(GlobalCtl* g, int32_t code) {
   int32_t expected = 0;
   __hip_atomic_compare_exchange_strong(&g->error, &expected, code, __ATOMIC_RELAXED,
@@ -184,19 +163,6 @@ __device__ __forceinline__ bool poll_abort(const ComponentParams& P, Lds& S, Ctx
 }
 
 __device__ __forceinline__ uint32_t bit_of(uint32_t x) { return 1u << (x & 31u); }
-
-// x added to *p by one lane (the compiler would wrap a plain atomic of one
-// lane in a second reduction over the wave, 2 % of the 223 x 227 grid's time).
-__device__ __forceinline__ int32_t lds_add(int32_t* p, int32_t x) {
-  const uint32_t at = static_cast<uint32_t>(
-      reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) int32_t*)p));
-  int32_t old;
-  asm volatile("ds_add_rtn_u32 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)"
-               : "=&v"(old)
-               : "v"(at), "v"(x)
-               : "memory");
-  return old;
-}
 
 // Which of the wave's active lanes' kN entries are new in a search: their
 // bits are set here, and *base is the first of the places reserved for them

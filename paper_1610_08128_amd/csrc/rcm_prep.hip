@@ -158,35 +158,6 @@ __global__ void k_validate_scan(int32_t n, int32_t nnz, const int32_t* __restric
 // us, 59 with eight lanes a row).
 constexpr uint32_t kNoColumn = 0x80000000u;  // above every column
 
-template <int kCtrl>
-__device__ __forceinline__ uint32_t dpp(uint32_t x) {
-  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
-      static_cast<int>(x), static_cast<int>(x), kCtrl, 0xf, 0xf, false));
-}
-// Equal pairs within a row's first or second 16 entries, and between them:
-// one side rotated by every step.
-template <int kStep>
-__device__ __forceinline__ uint32_t same_in(uint32_t x) {
-  if constexpr (kStep > 8) return 0u;
-  else return (x == dpp<0x120 + kStep>(x) ? 1u : 0u) | same_in<kStep + 1>(x);
-}
-template <int kStep>
-__device__ __forceinline__ uint32_t same_between(uint32_t x, uint32_t y) {
-  if constexpr (kStep > 15) return 0u;
-  else return (x == dpp<0x120 + kStep>(y) ? 1u : 0u) | same_between<kStep + 1>(x, y);
-}
-// The least value of the 16 lanes, in all of them.
-__device__ __forceinline__ uint32_t group_min(uint32_t x) {
-  uint32_t y = dpp<0xB1>(x);  // quad_perm: lane ^ 1
-  x = y < x ? y : x;
-  y = dpp<0x4E>(x);           // quad_perm: lane ^ 2
-  x = y < x ? y : x;
-  y = dpp<0x141>(x);          // row_half_mirror
-  x = y < x ? y : x;
-  y = dpp<0x140>(x);          // row_mirror
-  return y < x ? y : x;
-}
-
 __global__ void __launch_bounds__(kThreads)
 k_validate_long(int32_t n, int32_t nnz, const int32_t* __restrict__ rowptr,
                 const int32_t* __restrict__ colidx, int4* __restrict__ vinfo,
@@ -282,7 +253,7 @@ k_validate_long(int32_t n, int32_t nnz, const int32_t* __restrict__ rowptr,
         }
       }
       const bool diag = (__ballot(self) & group) != 0;
-      mn = group_min(mn);
+      mn = row_min(mn);
       if (sub == 0 && act) {
         vinfo[i] = broken ? make_int4(0, 0, 0, i) : make_int4(a, b, len - (diag ? 1 : 0), i);
         beta[i] = broken ? 0 : i - static_cast<int32_t>(mn);
@@ -938,7 +909,6 @@ __global__ void k_singletons(const CompTask* __restrict__ tasks, int32_t count,
 // In the input's order, which streams the rows, every gather missed: the
 // 128^3 grid took 226 us for its statistics, 150 us for this kernel on the
 // CSR, 96 us on the fixed-stride rows.
-constexpr int kXcds = 8;
 constexpr int kBetaLanes = 8;
 constexpr int kBetaUnroll = 4;
 constexpr int kBetaGroups = kThreads / kBetaLanes;
@@ -953,9 +923,7 @@ k_beta_after(int32_t n, int32_t nnz, const int32_t* __restrict__ rowptr,
              const int32_t* __restrict__ perm, const int32_t* __restrict__ iperm,
              int32_t* __restrict__ beta) {
   static_assert(kEllWidth == kBetaLanes, "an entry a lane");
-  const int64_t per = gridDim.x / kXcds;
-  const int64_t tile = static_cast<int64_t>(blockIdx.x % kXcds) * per + blockIdx.x / kXcds;
-  const int64_t k0 = tile * kBetaTile + threadIdx.x / kBetaLanes;
+  const int64_t k0 = xcd_tile() * kBetaTile + threadIdx.x / kBetaLanes;
   const uint32_t sub = threadIdx.x % kBetaLanes;
   // (unsigned: the last rows of nearly 2^31 entries reach past that)
   uint32_t a[kBetaUnroll], b[kBetaUnroll];
@@ -1186,7 +1154,7 @@ hipError_t launch_singletons(const CompTask* tasks, int32_t count, int32_t* perm
 hipError_t launch_bw_after(const Graph& g, const int4* ell, const int32_t* perm,
                            const int32_t* iperm, int32_t* beta, SegStats* seg, hipStream_t s) {
   const int64_t tiles = (static_cast<int64_t>(g.n) + kBetaTile - 1) / kBetaTile;
-  const unsigned blocks = static_cast<unsigned>((tiles + kXcds - 1) / kXcds * kXcds);
+  const unsigned blocks = xcd_grid(tiles);
   if (ell)
     k_beta_after<true><<<blocks, kThreads, 0, s>>>(g.n, g.nnz, g.rowptr, g.colidx,
                                                    reinterpret_cast<const int32_t*>(ell), perm,

@@ -185,9 +185,6 @@ __device__ __forceinline__ uint32_t ell_level_key(const ELds& L, int32_t b, int3
   return wave_min_u32(k);
 }
 
-// A value that is the same in every lane, as a scalar.
-__device__ __forceinline__ int32_t uniform(int32_t x) { return __builtin_amdgcn_readfirstlane(x); }
-
 // One level of at most kChunks * 64 / LPV vertices ord[b, e), either kind of
 // pass, every chunk in registers: lanes past the level stand for its last
 // vertex.  A search marks with the least word of its pass, and the lane that

@@ -86,24 +86,6 @@ struct WPass {
   int32_t ecc, root, count;
 };
 
-__device__ __forceinline__ int32_t uniform(int32_t x) { return __builtin_amdgcn_readfirstlane(x); }
-
-template <int kCtrl>
-__device__ __forceinline__ uint32_t dpp(uint32_t x) {
-  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
-      static_cast<int>(x), static_cast<int>(x), kCtrl, 0xf, 0xf, false));
-}
-// Minimum over the 16 lanes of a DPP row, in every lane of it.
-__device__ __forceinline__ uint32_t row_min(uint32_t x) {
-  uint32_t y = dpp<0xB1>(x);   // quad_perm: lane ^ 1
-  x = y < x ? y : x;
-  y = dpp<0x4E>(x);            // quad_perm: lane ^ 2
-  x = y < x ? y : x;
-  y = dpp<0x141>(x);           // row_half_mirror
-  x = y < x ? y : x;
-  y = dpp<0x140>(x);           // row_mirror
-  return y < x ? y : x;
-}
 __device__ __forceinline__ uint32_t wave_min(uint32_t x) {
   x = row_min(x);
   uint32_t r = kFree;
@@ -113,30 +95,6 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t x) {
     r = y < r ? y : r;
   }
   return r;
-}
-// Inclusive prefix sum within a wave by DPP row shifts and broadcasts.
-__device__ __forceinline__ int wave_scan(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
-  return x;
-}
-
-// Equal pairs among a row's entries: x0 holds entries 0 .. 15 in the 16 lanes,
-// x1 entries 16 .. 31 (lanes past the row's end hold distinct fillers); each
-// pair is compared by rotating one side.
-template <int kStep>
-__device__ __forceinline__ uint32_t same_in(uint32_t x) {
-  if constexpr (kStep > 8) return 0u;
-  else return (x == dpp<0x120 + kStep>(x) ? 1u : 0u) | same_in<kStep + 1>(x);
-}
-template <int kStep>
-__device__ __forceinline__ uint32_t same_between(uint32_t x, uint32_t y) {
-  if constexpr (kStep > 15) return 0u;
-  else return (x == dpp<0x120 + kStep>(y) ? 1u : 0u) | same_between<kStep + 1>(x, y);
 }
 
 // Degrees, repeated columns, bandwidth and profile of the input order, from
@@ -294,19 +252,6 @@ __device__ __forceinline__ void sort_by_degree(const WLds& L, WShared& S, int32_
             static_cast<uint16_t>(id[j]);
     __syncthreads();
   }
-}
-
-// x added to *p, once per call: one lane makes it (the compiler would wrap
-// a plain atomic of one lane in a second reduction over the wave).
-__device__ __forceinline__ int32_t lds_add(int32_t* p, int32_t x) {
-  const uint32_t at = static_cast<uint32_t>(
-      reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) int32_t*)p));
-  int32_t old;
-  asm volatile("ds_add_rtn_u32 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)"
-               : "=&v"(old)
-               : "v"(at), "v"(x)
-               : "memory");
-  return old;
 }
 
 // The unvisited neighbours of the level ord[fb, fe): marked (search: with the

@@ -347,7 +347,6 @@ __device__ int32_t wlevel(const WLds& L, const WinParams& P, int32_t w_lo, int32
 }
 
 // Minimum and maximum over a wave: within the DPP rows, then the four of them.
-__device__ __forceinline__ int32_t uniform(int32_t x) { return __builtin_amdgcn_readfirstlane(x); }
 template <int kCtrl>
 __device__ __forceinline__ int32_t dpp_of(int32_t x) {
   return __builtin_amdgcn_update_dpp(x, x, kCtrl, 0xf, 0xf, false);
