@@ -100,8 +100,9 @@ inline bool window_enabled() {
 // Auto team size of a single graph: all compute units, on which its
 // asynchronous search passes spread (the two of the 40^3 / 60 x 60 x 61 grids
 // on 64, 128 and 256 work-groups: 0.62, 0.59, 0.57 / 1.04, 0.91, 0.84 ms; of
-// the 400^2 grid 2.98, 2.57, 2.52), the labelled levels being label_team's; 64
-// for a graph so small that a level hardly fills those.
+// the 400^2 grid 2.98, 2.57, 2.52; only levels of one or two vertices lose, a
+// path of 40,000 in a level order 146 -> 152), the labelled levels being
+// label_team's; 64 for a graph so small that a level hardly fills those.
 inline int team_for(const Opts& o, int64_t n) {
   if (o.team_size > 0) return o.team_size;
   return n >= (1 << 15) ? 256 : 64;
